@@ -512,7 +512,7 @@ const char* tb_last_error(void);
  * tb_debug_select_kernels — force a kernel family so that tests can compare
  * every path: greedy 0 = automatic choice, 1 = the reference kernel (one
  * workgroup per stream, any V); beam 0 = automatic, 1 = the reference kernel,
- * 2 = automatic but never the helper-wave kernel. TB_EINVAL for other values.
+ * 2 = as 0. TB_EINVAL for other values.
  *
  * tb_debug_set_spin_limit — polls after which the greedy hand-off wait (the
  * waves of a workgroup pass exact states in order) gives up and writes

@@ -1,4 +1,5 @@
-// Boosted beam step (reference kernel): one workgroup per stream.
+// Boosted beam step: the dispatch, and the reference kernel, one workgroup per
+// stream, that tests compare the step kernel (beam_list.hpp) with.
 //
 // For each of the K hypotheses of a stream the workgroup forms the row's
 // log-sum-exp (float64 sum and log, rounded once to float32), the boosted keys
@@ -10,9 +11,7 @@
 // graph states (Sec. II-C: scores and states carried across calls).
 #include <climits>
 
-#include "beam_fast.hpp"
-#include "beam_pipe.hpp"
-#include "beam_wide.hpp"
+#include "beam_rows.hpp"
 #include "device.hpp"
 #include "ref_table.hpp"
 #include "launch.hpp"
@@ -76,20 +75,19 @@ __device__ inline int32_t ac_move(const ArenaView& A, int32_t off, int32_t x, in
   }
 }
 
-// With STREAM, the streaming beam (tb_boost_step_beam_stream) for rows and
-// beams the one-wave-per-hypothesis kernel does not take: every hypothesis'
+// With STREAM, the streaming beam (tb_boost_step_beam_stream): every hypothesis'
 // normaliser first, then the recombination of equal label sequences (x's
 // blank extension and the extension of x's prefix slot y by x's last label:
 // the better in (value, flat index) order gets log(e^a + e^b), the other
 // -inf), applied to the candidates as they are formed; hashes and tree
-// records as in the fast kernel.
+// records as in the step kernel.
 template <class Ld, int MAXK, bool STREAM>
 __global__ __launch_bounds__(kThreads) void beam_ref_kernel(
     ArenaView A, const typename Ld::T* __restrict__ logits, int32_t T, int32_t B, int32_t K,
     int64_t stride, const int32_t* __restrict__ model_ids, int32_t* __restrict__ states,
     float* __restrict__ scores, int32_t* __restrict__ out_tok, int32_t* __restrict__ out_parent,
     int32_t* __restrict__ out_state, float* __restrict__ out_step, float* __restrict__ out_cum,
-    beamk::StreamArgs sa) {
+    StreamArgs sa) {
   extern __shared__ int32_t smem[];
   lds_poison(smem, ref_table_bytes(A.V1 - 1));  // the launch's dynamic LDS
   const int32_t V1 = A.V1, V = V1 - 1;
@@ -193,7 +191,7 @@ __global__ __launch_bounds__(kThreads) void beam_ref_kernel(
             const float a = cx + (Ld::get(row_of(x), V) + sh_phi[x]);
             const float bv = cy + (Ld::get(row_of(y), v) + psi_x);
             if (a > -__builtin_huge_valf() && bv > -__builtin_huge_valf()) {
-              const float merged = beamk::logaddexp32(a, bv);
+              const float merged = blist::logaddexp32(a, bv);
               const bool keep_a = a > bv || (a == bv && x * V1 + V < y * V1 + v);
               blank_set[x] = 1;
               blank_val[x] = keep_a ? merged : -__builtin_huge_valf();
@@ -386,7 +384,7 @@ template <class Ld, int MAXK, bool STREAM>
 void launch_t(const ArenaView& A, const void* logits, int32_t T, int32_t B, int32_t K,
               int64_t stride, const int32_t* model_ids, int32_t* states, float* scores,
               int32_t* out_tok, int32_t* out_parent, int32_t* out_state, float* out_step,
-              float* out_cum, hipStream_t st, beamk::StreamArgs sa) {
+              float* out_cum, hipStream_t st, StreamArgs sa) {
   const size_t lds = ref_table_bytes(A.V1 - 1);
   allow_dynamic_lds(&beam_ref_kernel<Ld, MAXK, STREAM>, lds);
   hipLaunchKernelGGL((beam_ref_kernel<Ld, MAXK, STREAM>), dim3(B), dim3(kThreads), lds, st, A,
@@ -398,7 +396,7 @@ template <class Ld, bool STREAM = false>
 void launch_k(const ArenaView& A, const void* logits, int32_t T, int32_t B, int32_t K,
               int64_t stride, const int32_t* model_ids, int32_t* states, float* scores,
               int32_t* out_tok, int32_t* out_parent, int32_t* out_state, float* out_step,
-              float* out_cum, hipStream_t st, beamk::StreamArgs sa = beamk::StreamArgs{}) {
+              float* out_cum, hipStream_t st, StreamArgs sa = StreamArgs{}) {
   if (K <= 2)
     launch_t<Ld, 2, STREAM>(A, logits, T, B, K, stride, model_ids, states, scores, out_tok,
                             out_parent, out_state, out_step, out_cum, st, sa);
@@ -418,48 +416,33 @@ void launch_k(const ArenaView& A, const void* logits, int32_t T, int32_t B, int3
 
 }  // namespace
 
-// Kernel choice: the helper-wave kernel serves V+1 > 2048 with K <= 4 (rows
-// up to 4224 float32 or 8320 bfloat16 tokens, where its two-slot LDS ring
-// fits); the one-wave-per-hypothesis kernel serves V+1 <= 2048 with K <= 8
-// (override sets that fit its lists); the wide-row kernel serves K <= 8 and
-// V+1 in (2048, 256 * 41]; the reference kernel serves the rest. Tests can
-// force the reference kernel, or skip the helper-wave kernel, through
-// tb_debug_select_kernels.
+// Row summaries, then the step kernel (beam_rows.hpp, beam_list.hpp).
+static hipError_t launch_list(const ArenaView& A, const void* logits, int32_t dtype, int32_t T,
+                              int32_t B, int32_t K, int64_t row_stride, const int32_t* model_ids,
+                              int32_t* states, float* scores, int32_t* out_tok,
+                              int32_t* out_parent, int32_t* out_state, float* out_step,
+                              float* out_cum, bool stream, StreamArgs sa, hipStream_t st) {
+  const bool f32 = dtype == TB_F32;
+  const blist::RowsLaunch rows =
+      f32 ? blist::rows_launcher_f32(A.V1) : blist::rows_launcher_bf16(A.V1);
+  const hipError_t e = rows(A, logits, T, B, K, row_stride, model_ids, states, out_tok,
+                            out_parent, out_state, out_step, out_cum, st);
+  if (e != hipSuccess) return e;
+  const bool in_lds = blist::rows_in_lds(A.V1, K, f32 ? 4 : 2);
+  const blist::StepLaunch step = f32 ? blist::step_launcher_f32(K, stream, in_lds)
+                                     : blist::step_launcher_bf16(K, stream, in_lds);
+  return step(A, logits, T, B, K, row_stride, model_ids, states, scores, out_tok, out_parent,
+              out_state, out_step, out_cum, sa, st);
+}
+
+// The reference kernel serves only tests, through tb_debug_select_kernels.
 hipError_t launch_beam(const ArenaView& A, const void* logits, int32_t dtype, int32_t T, int32_t B,
                        int32_t K, int64_t row_stride, const int32_t* model_ids, int32_t* states,
                        float* scores, int32_t* out_tok, int32_t* out_parent, int32_t* out_state,
                        float* out_step, float* out_cum, hipStream_t st) {
-  const int32_t choice = debug_beam_kernel();
-  const bool ref = choice == kBeamRef;
-  const bool nopipe = choice == kBeamNoPipe;
-  if (!ref && !nopipe && K <= 8) {
-    bpipe::PipeLaunch f = dtype == TB_F32 ? bpipe::pipe_launcher_f32(A.V1, K)
-                                          : bpipe::pipe_launcher_bf16(A.V1, K);
-    if (f)
-      return f(A, logits, T, B, K, row_stride, model_ids, states, scores, out_tok, out_parent,
-               out_state, out_step, out_cum, st);
-  }
-  if (!ref && K <= 8 && A.V1 >= 2 && A.V1 <= 64 * 32 && A.max_override <= beamk::kOverCap) {
-    const int per = (A.V1 + 63) / 64;
-    const int maxk = K <= 2 ? 2 : (K <= 4 ? 4 : 8);
-    beamk::BeamLaunch f = per <= 8    ? beamk::beam_launcher_1_8(per, maxk, dtype)
-                          : per <= 16 ? beamk::beam_launcher_9_16(per, maxk, dtype)
-                          : per <= 24 ? beamk::beam_launcher_17_24(per, maxk, dtype)
-                                      : beamk::beam_launcher_25_32(per, maxk, dtype);
-    if (f)
-      return f(A, logits, T, B, K, row_stride, model_ids, states, scores, out_tok, out_parent,
-               out_state, out_step, out_cum, st);
-  }
-  if (!ref && K <= 8 && A.V1 > 64 * 32 && A.V1 <= wide::kThreads * 41 &&
-      wide::lds_bytes(A) <= 60 * 1024) {
-    const int tpv = (A.V1 + wide::kThreads - 1) / wide::kThreads;
-    const int maxk = K <= 4 ? 4 : 8;
-    wide::BeamWideLaunch f = dtype == TB_F32 ? wide::beam_wide_launcher_f32(tpv, maxk)
-                                             : wide::beam_wide_launcher_bf16(tpv, maxk);
-    if (f)
-      return f(A, logits, T, B, K, row_stride, model_ids, states, scores, out_tok, out_parent,
-               out_state, out_step, out_cum, st);
-  }
+  if (debug_beam_kernel() != kBeamRef)
+    return launch_list(A, logits, dtype, T, B, K, row_stride, model_ids, states, scores, out_tok,
+                       out_parent, out_state, out_step, out_cum, false, StreamArgs{}, st);
   if (dtype == TB_F32)
     launch_k<LoadF32>(A, logits, T, B, K, row_stride, model_ids, states, scores, out_tok,
                       out_parent, out_state, out_step, out_cum, st);
@@ -469,38 +452,21 @@ hipError_t launch_beam(const ArenaView& A, const void* logits, int32_t dtype, in
   return hipGetLastError();
 }
 
-// The streaming beam runs the one-wave-per-hypothesis kernel with the
-// recombination and tree stages where that kernel applies (K <= 8, V+1 <=
-// 2048, override sets within its lists), else the reference kernel's.
-bool beam_stream_supported(int32_t v_plus_blank, int32_t max_override, int32_t K) {
-  if (K < 1 || K > 8 || v_plus_blank < 2 || v_plus_blank > 64 * 32 || K > v_plus_blank)
-    return false;
-  return max_override <= beamk::kOverCap;
-}
-
 hipError_t launch_beam_stream(const ArenaView& A, const void* logits, int32_t dtype, int32_t T,
                               int32_t B, int32_t K, int64_t row_stride, const int32_t* model_ids,
                               int32_t* states, float* scores, tb_hyp* hyps, int32_t* tree,
                               int32_t tree_cap, int32_t* tree_len, int32_t recombine,
                               int32_t* out_tok, int32_t* out_parent, int32_t* out_state,
                               float* out_step, float* out_cum, hipStream_t st) {
-  beamk::StreamArgs sa;
+  StreamArgs sa;
   sa.hyps = hyps;
   sa.tree = tree;
   sa.cap = tree_cap;
   sa.tree_len = tree_len;
   sa.recombine = recombine;
-  if (debug_beam_kernel() != kBeamRef && beam_stream_supported(A.V1, A.max_override, K)) {
-    const int per = (A.V1 + 63) / 64;
-    beamk::BeamStreamLaunch f = per <= 8    ? beamk::beam_stream_launcher_1_8(per, dtype)
-                                : per <= 16 ? beamk::beam_stream_launcher_9_16(per, dtype)
-                                : per <= 24 ? beamk::beam_stream_launcher_17_24(per, dtype)
-                                            : beamk::beam_stream_launcher_25_32(per, dtype);
-    if (f)
-      return f(A, logits, T, B, K, row_stride, model_ids, states, scores, out_tok, out_parent,
-               out_state, out_step, out_cum, st, sa);
-  }
-  // any other row width, beam or override set: the reference kernel's stage
+  if (debug_beam_kernel() != kBeamRef)
+    return launch_list(A, logits, dtype, T, B, K, row_stride, model_ids, states, scores, out_tok,
+                       out_parent, out_state, out_step, out_cum, true, sa, st);
   if (dtype == TB_F32)
     launch_k<LoadF32, true>(A, logits, T, B, K, row_stride, model_ids, states, scores, out_tok,
                             out_parent, out_state, out_step, out_cum, st, sa);

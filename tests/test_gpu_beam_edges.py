@@ -1,0 +1,113 @@
+"""The beam kernels where their instances and paths change, against the oracle:
+rows on both sides of every row-preparation instance, beams on both sides of
+every wave layout (4, 8 and 16 waves, two slots a wave), calls with and without
+LDS records, rows of equal values (more candidates than the ranked list holds),
+rows with fewer finite values than hypotheses (the rounds over every
+candidate), and a row with a nan beside clean streams. Tokens, parents, states
+and accumulated scores bit for bit; step scores within 1e-5 (float32 sums of
+terms below 64: 64 * 2^-24 * 2 = 8e-6)."""
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from tests.gpu_cases import compare_beam, gpu_beam, say
+
+pytestmark = pytest.mark.gpu
+
+ATOL = 1e-5
+EDGES = [2, 3, 256, 257, 512, 513, 768, 769, 1024, 1025, 1280, 1281, 1536, 1537, 1792, 1793, 2048,
+         2049, 3072, 3073, 4096, 4097, 5120, 5121, 6144, 6145, 8192, 8193, 10240, 10241, 16384,
+         16385]
+BEAMS = [8, 1, 4, 5, 9, 16, 17, 32, 12, 3]
+
+
+def _run(V1, K, kind, fill, dtype, chunk, T=6):
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    from workloads.synth import _f32_to_bf16_bits
+    K = min(K, V1)
+    V = V1 - 1
+    say(f"[beam edge] V+1={V1} K={K} {kind} {fill} {dtype} chunk={chunk}")
+    cfg = W.Config(8100 + V1 + K, "edge", B=3, K=K, V=V, T=T, chunk=chunk, dtype="f32",
+                   n_phrases=40, len_lo=1, len_hi=5, token_dist="zipf", zipf_s=1.1, logit_std=1.5,
+                   blank_offset=0.5, n_case=V // 6)
+    lists, cm = W.phrases(cfg), W.class_map(cfg)
+    mids = np.array([0, 1, -1], np.int32)
+    rows = np.array(W.logits(cfg))
+    rng = np.random.default_rng(V1 * 64 + K)
+    for b in range(2):  # spell phrases, so that states have children
+        t = 0
+        while t < T:
+            ph = lists[b][int(rng.integers(len(lists[b])))]
+            for i, v in enumerate(ph[:T - t]):
+                rows[t + i, b, :, int(v)] += np.float32(4.0)
+            t += len(ph)
+    if fill == "equal":
+        rows[...] = np.float32(0.25)
+    elif fill == "masked":
+        keep = rng.random(rows.shape) < min(1.0, 1.5 / V1)
+        keep[..., V] = rng.random(rows.shape[:-1]) < 0.5
+        keep[..., 0] |= ~keep.any(-1)
+        rows[~keep] = -np.inf
+    if dtype == "bf16":
+        rows = _f32_to_bf16_bits(rows)
+    dec = BoostDecoder(lists, cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+    graphs = {m: oracle.build_graph(lists[m], cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+              for m in (0, 1)}
+    dev = to_device_logits(rows)
+    if kind == "plain":
+        st0, S0 = oracle.init_carry(mids, K)
+        compare_beam(gpu_beam(dec, dev, mids, chunk),
+                     oracle.beam_decode(graphs, mids, rows, st0, S0), range(cfg.B), ATOL)
+        return
+    carry, want = dec.start_beam_stream(mids, K, 24), oracle.init_stream_carry(mids, K)
+    for t0 in range(0, T, chunk):
+        got = [o.cpu().numpy() for o in dec.beam_stream(dev[t0:t0 + chunk], carry)]
+        exp = oracle.beam_decode_stream(graphs, mids, rows[t0:t0 + chunk], want, tree_cap=24)
+        compare_beam(got, exp, range(cfg.B), ATOL)
+
+
+@pytest.mark.parametrize("i", range(len(EDGES)))
+def test_row_instance_edges(i):
+    _run(EDGES[i], BEAMS[i % len(BEAMS)], ("plain", "stream")[i % 2], "normal",
+         ("f32", "bf16")[i // 2 % 2], (6, 2)[i // 3 % 2])
+
+
+@pytest.mark.parametrize("K", [1, 4, 5, 8, 9, 16, 17, 32])
+@pytest.mark.parametrize("kind", ["plain", "stream"])
+def test_wave_layouts(K, kind):
+    _run(601, K, kind, "normal", "f32", 6, T=10)
+    _run(2600, K, kind, "normal", "bf16", 10, T=10)
+
+
+@pytest.mark.parametrize("K", [3, 8, 16, 32])
+@pytest.mark.parametrize("fill", ["equal", "masked"])
+@pytest.mark.parametrize("V1", [70, 1025, 2305])
+def test_equal_and_masked_rows(V1, fill, K):
+    for kind in ("plain", "stream"):
+        _run(V1, K, kind, fill, "f32", 3)
+
+
+@pytest.mark.parametrize("V1", [300, 2305])
+def test_nan_row_leaves_other_streams(V1):
+    """A nan in one stream's row leaves the other streams' outputs as they are,
+    and the stream's own outputs hold valid tokens, parents and states."""
+    import torch
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    cfg = W.Config(8800 + V1, "nan", B=3, K=5, V=V1 - 1, T=5, chunk=5, dtype="f32", n_phrases=20,
+                   len_lo=1, len_hi=4, token_dist="zipf", zipf_s=1.1, logit_std=1.0,
+                   blank_offset=0.0, n_case=V1 // 6)
+    lists = W.phrases(cfg)
+    dec = BoostDecoder(lists, W.class_map(cfg))
+    rows = np.array(W.logits(cfg))
+    mids = np.arange(3, dtype=np.int32)
+    clean = gpu_beam(dec, to_device_logits(rows), mids, 5)
+    rows[2, 1, 3, 7] = np.nan
+    got = gpu_beam(dec, to_device_logits(rows), mids, 5)
+    torch.cuda.synchronize()
+    for a, b in zip(clean, got):
+        a, b = np.asarray(a).reshape(-1, 3, 5)[:5], np.asarray(b).reshape(-1, 3, 5)[:5]
+        assert np.array_equal(a[:, [0, 2]], b[:, [0, 2]])
+    tok, par = (np.asarray(got[i]).reshape(-1, 3, 5) for i in (0, 1))
+    assert tok.min() >= 0 and tok.max() <= cfg.V and par.min() >= 0 and par.max() < 5
