@@ -208,6 +208,17 @@ struct Graph {
 __device__ __forceinline__ int32_t arc_class(uint2 m) { return (int32_t)((m.y >> 16) & 0x7fffu); }
 __device__ __forceinline__ bool arc_more(uint2 m) { return (m.y >> 31) != 0u; }
 
+// The 16-byte LDS record of global state x: first child | child count << 16 |
+// psi index << 24, link | phi index << 16, the arc record. False when a field
+// does not fit.
+__device__ __forceinline__ bool hot_record(const ArenaView& A, int64_t x, uint4& out) {
+  const uint32_t* r = A.state_rec + 3 * x;
+  const uint32_t* q = A.arc_mem + 2 * x;
+  const uint32_t r2 = r[2];
+  out = make_uint4(r[0], (r[1] & 0xffffu) | (((r2 >> 8) & 0xffu) << 16), q[0], q[1]);
+  return (r2 >> 31) == 0u;
+}
+
 constexpr int kLevels = 4;  // chain states whose children are taken one per lane
 
 // What a wave holds of one of its slots during a step.
@@ -296,11 +307,8 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
   int32_t nhot = biased ? (n < lay.nhot ? n : lay.nhot) : 0;
   bool unusable = false;
   for (int32_t i = threadIdx.x; i < nhot; i += 64 * NW) {
-    const uint32_t* r = A.state_rec + 3 * ((int64_t)off + i);
-    const uint32_t* q = A.arc_mem + 2 * ((int64_t)off + i);
-    const uint32_t r2 = r[2];
-    hot[i] = make_uint4(r[0], (r[1] & 0xffffu) | (((r2 >> 8) & 0xffu) << 16), q[0], q[1]);
-    unusable = unusable || (i > 0 && (r2 >> 31));
+    const bool ok = hot_record(A, (int64_t)off + i, hot[i]);
+    unusable = unusable || (i > 0 && !ok);
   }
   if (nhot > 0) {
     const float* vt = A.value_tab + 512 * (int64_t)m;

@@ -1,0 +1,107 @@
+"""The wide-row greedy kernels where their instances and paths change, against
+the oracle: rows on both sides of every summary instance, calls with and
+without LDS records and longer than one piece of LDS row records, rows of
+equal values, rows with few finite values or none, and a row with a nan beside
+clean streams. Tokens and states bit for bit, scores within 1e-5 (float32 sums
+of terms below 64: 64 * 2^-24 * 2 = 8e-6)."""
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from tests.gpu_cases import compare_greedy, gpu_greedy, say
+
+pytestmark = pytest.mark.gpu
+
+ATOL = 1e-5
+EDGES = [2049, 3072, 3073, 4096, 4097, 5120, 5121, 6144, 6145, 8192, 8193, 10240, 10241, 16384,
+         16385, 32768]
+
+
+def _case(V1, T, fill, dtype, seed=0):
+    from workloads.synth import _f32_to_bf16_bits
+    V = V1 - 1
+    cfg = W.Config(8200 + V1 + seed, "edge", B=4, K=1, V=V, T=T, chunk=T, dtype="f32",
+                   n_phrases=150, len_lo=1, len_hi=7, token_dist="zipf", zipf_s=1.2, logit_std=1.0,
+                   blank_offset=1.0, n_case=V // 6)
+    lists, cm = [list(p) for p in W.phrases(cfg)], W.class_map(cfg)
+    # nested suffixes: chains of more than four states
+    lists[1] += [lists[1][0][i:] for i in range(len(lists[1][0]))]
+    long = np.arange(40, 52, dtype=np.int32)
+    lists[1] += [long[i:] for i in range(len(long))]
+    if seed % 2:  # classes of five members
+        n5 = V // 7
+        cm = np.arange(V + 1, dtype=np.int32)
+        for k in range(1, 5):
+            cm[k * n5:(k + 1) * n5] = np.arange(n5)
+        cm[V] = -1
+    mids = np.array([0, 1, -1, 3], np.int32)
+    rows = np.array(W.logits(cfg))[:, :, 0]
+    rng = np.random.default_rng(V1 + 7 * T)
+    for b in (0, 1, 3):
+        t = 0
+        while t < T:
+            ph = lists[b][int(rng.integers(len(lists[b])))]
+            for i, v in enumerate(ph[:T - t]):
+                rows[t + i, b, int(v)] += np.float32(4.0)
+            t += len(ph)
+    if fill == "equal":
+        rows[...] = np.float32(0.25)
+    elif fill == "masked":
+        keep = rng.random(rows.shape) < 2.0 / V1
+        keep[..., V] = rng.random(rows.shape[:-1]) < 0.5
+        keep[..., 5] |= ~keep.any(-1)
+        rows[~keep] = -np.inf
+    if dtype == "bf16":
+        rows = _f32_to_bf16_bits(rows)
+    return cfg, lists, cm, mids, rows
+
+
+def _check(V1, T, chunk, fill, dtype, seed=0):
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    say(f"[greedy edge] V+1={V1} T={T} chunk={chunk} {fill} {dtype}")
+    cfg, lists, cm, mids, rows = _case(V1, T, fill, dtype, seed)
+    dec = BoostDecoder(lists, cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+    graphs = {m: oracle.build_graph(lists[m], cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+              for m in (0, 1, 3)}
+    st0 = np.where(mids >= 0, 0, -1).astype(np.int32)
+    compare_greedy(gpu_greedy(dec, to_device_logits(rows), mids, chunk),
+                   oracle.greedy_decode(graphs, mids, rows, st0), range(cfg.B), ATOL)
+
+
+@pytest.mark.parametrize("i", range(len(EDGES)))
+def test_row_instance_edges(i):
+    _check(EDGES[i], 20, (20, 7, 1)[i % 3], "normal", ("f32", "bf16")[i % 2], i)
+    _check(EDGES[i], 3, 3, "normal", ("bf16", "f32")[i % 2], i)
+
+
+@pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 63, 64, 65, 200])
+def test_call_lengths(T):
+    _check(2305, T, T, "normal", "f32", T)
+
+
+def test_call_of_several_pieces():
+    """More steps than LDS holds row records for (48 bytes each)."""
+    _check(2049, 3500, 3500, "normal", "bf16")
+
+
+@pytest.mark.parametrize("fill", ["equal", "masked"])
+@pytest.mark.parametrize("V1", [2049, 4100, 8193])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_equal_and_masked_rows(V1, fill, dtype):
+    _check(V1, 12, 12, fill, dtype, 1)
+    _check(V1, 12, 12, fill, dtype, 2)
+
+
+@pytest.mark.parametrize("V1", [300, 2305])
+def test_nan_row_leaves_other_streams(V1):
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    cfg, lists, cm, mids, rows = _case(V1, 18, "normal", "f32")
+    dec = BoostDecoder(lists, cm)
+    clean = gpu_greedy(dec, to_device_logits(rows), mids, 18)
+    rows[7, 1, 9] = np.nan
+    got = gpu_greedy(dec, to_device_logits(rows), mids, 18)
+    for a, b in zip(clean[:3], got[:3]):
+        assert np.array_equal(a[:, [0, 2, 3]], b[:, [0, 2, 3]])
+    assert got[0].min() >= 0 and got[0].max() <= cfg.V
