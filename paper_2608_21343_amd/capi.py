@@ -165,10 +165,26 @@ def _need(t, n: int, name: str, exact: bool = True) -> None:
         raise ValueError(f"{name} holds {k} elements, needs {'' if exact else 'at least '}{n}")
 
 
+def _buf(t, n: int, dtype, name: str, exact: bool = False) -> int:
+    """_need and _dptr of a required buffer in one call: the step calls of a
+    frame-synchronous decoder are bound by this marshalling."""
+    if t is None:
+        raise ValueError(f"{name} is required")
+    k = t.numel()
+    if k < n or (exact and k != n) or not (t.is_cuda and t.dtype == dtype and t.is_contiguous()):
+        _need(t, n, name, exact)
+        _dptr(t, dtype, name)
+    return t.data_ptr()
+
+
 def _stream(stream) -> Optional[int]:
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    # the handle of torch.cuda.current_stream() without making its object
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 # ---------------------------------------------------------------------------
@@ -371,37 +387,36 @@ def tb_boost_step_greedy(arena: Arena, logits, model_ids, states, out_tok, out_s
     """logits: [T, B, V+1] (or [T, B, 1, V+1]) device tensor, rows contiguous."""
     import torch
     dt, rs = _logits_args(logits)
-    if logits.dim() == 4:
-        if logits.shape[2] != 1:
+    shape = logits.shape
+    if len(shape) == 4:
+        if shape[2] != 1:
             raise ValueError("greedy logits must have K = 1")
         rs = logits.stride(1)
-    if logits.dim() not in (3, 4):
+    elif len(shape) != 3:
         raise ValueError("greedy logits must be [T, B, V+1] or [T, B, 1, V+1]")
-    if logits.shape[-1] != arena.layout.v_plus_blank:
-        raise ValueError(f"logits rows hold {logits.shape[-1]} values, the arena has "
+    if shape[-1] != arena.layout.v_plus_blank:
+        raise ValueError(f"logits rows hold {shape[-1]} values, the arena has "
                          f"V+1 = {arena.layout.v_plus_blank}")
-    if T is not None and not 0 <= T <= logits.shape[0]:
-        raise ValueError(f"T = {T} outside [0, {logits.shape[0]}]")
-    if B is not None and B != logits.shape[1]:
-        raise ValueError(f"B = {B} differs from the logits' {logits.shape[1]} streams")
-    T = logits.shape[0] if T is None else T
-    B = logits.shape[1]
+    if T is not None and not 0 <= T <= shape[0]:
+        raise ValueError(f"T = {T} outside [0, {shape[0]}]")
+    if B is not None and B != shape[1]:
+        raise ValueError(f"B = {B} differs from the logits' {shape[1]} streams")
+    T = shape[0] if T is None else T
+    B = shape[1]
     if T > 1 and logits.stride(0) != B * rs:
         raise ValueError("logits steps must be laid out as (t*B + b) * row_stride")
     if row_stride is not None and row_stride != rs:
         raise ValueError(f"row_stride {row_stride} differs from the logits' {rs}")
-    _need(model_ids, B, "model_ids")
-    _need(states, B, "states")
-    for name, o in (("out_tok", out_tok), ("out_state", out_state), ("out_score", out_score)):
-        _need(o, T * B, name, exact=False)
-    ptr = _logits_ptr(logits)
-    _check(LIB.tb_boost_step_greedy(C.byref(arena.arena), C.c_void_p(ptr), dt, T, B, rs,
-                                    _dptr(model_ids, torch.int32, "model_ids"),
-                                    _dptr(states, torch.int32, "states"),
-                                    _dptr(out_tok, torch.int32, "out_tok"),
-                                    _dptr(out_state, torch.int32, "out_state"),
-                                    _dptr(out_score, torch.float32, "out_score"),
-                                    _stream(stream)))
+    i32, n = torch.int32, T * B
+    mids = _buf(model_ids, B, i32, "model_ids", exact=True)
+    carry = _buf(states, B, i32, "states", exact=True)
+    tok = _buf(out_tok, n, i32, "out_tok")
+    sta = _buf(out_state, n, i32, "out_state")
+    sco = _buf(out_score, n, torch.float32, "out_score")
+    code = LIB.tb_boost_step_greedy(C.byref(arena.arena), _logits_ptr(logits), dt, T, B, rs, mids,
+                                    carry, tok, sta, sco, _stream(stream))
+    if code:
+        _check(code)
 
 
 def tb_boost_step_beam(arena: Arena, logits, model_ids, states, scores, out_tok, out_parent,
