@@ -1485,9 +1485,15 @@ __global__ __launch_bounds__(Shape<PER>::NT) void greedy_seg_kernel(
 
 // Repairs the workgroup boundaries of each stream after greedy_seg_kernel,
 // boundaries in order: from the exact state before a boundary, recompute
-// until the stored trajectory is met. Four waves fill the tables, wave 0
+// until the stored trajectory is met. All waves fill the tables, wave 0
 // repairs. Writes the carry.
-constexpr int kFixThreads = 256;
+// The fill bounds the kernel, and it is bound by the loads a CU has in flight:
+// a launch over rows of 1025 float32 takes 12.0 us with sixteen waves and took
+// 18.4 us with four (mean of 32 streams of 500 rows and 128 of 1024). The
+// repairing wave's three row buffers need more than the 128 registers that
+// sixteen waves leave it above 20 chunks: eight there.
+template <int PER>
+constexpr int fix_threads() { return PER <= 20 ? 1024 : 512; }
 constexpr int kFixHot = 6144;
 
 template <int PER>
@@ -1499,7 +1505,7 @@ struct alignas(16) FixLds {
 };
 
 template <class Ld, int PER>
-__global__ __launch_bounds__(kFixThreads) void greedy_fix_kernel(
+__global__ __launch_bounds__(fix_threads<PER>()) void greedy_fix_kernel(
     ArenaView A, const typename Ld::T* __restrict__ logits, int32_t T, int32_t B, int64_t stride,
     int32_t G, int32_t L, int32_t W, const int32_t* __restrict__ model_ids,
     int32_t* __restrict__ states, int32_t* __restrict__ out_tok, int32_t* __restrict__ out_state,
@@ -1527,8 +1533,8 @@ __global__ __launch_bounds__(kFixThreads) void greedy_fix_kernel(
     }
     const int32_t off = A.model_off[m], n = A.model_n[m];
     const int32_t nhot = n < kFixHot ? n : kFixHot;
-    fill_tables<PER, kFixThreads>(S.tab, A, m, 1);
-    fill_state_hot<kFixHot, kFixThreads>(S.hot, A, m, off, nhot);
+    fill_tables<PER, fix_threads<PER>()>(S.tab, A, m, 1);
+    fill_state_hot<kFixHot, fix_threads<PER>()>(S.hot, A, m, off, nhot);
     __syncthreads();
     if (threadIdx.x >= 64) return;  // no barrier follows
     const SGraph Gr(A, off, nhot, S.hot, S.tab);
@@ -1802,7 +1808,7 @@ hipError_t launch_seg(const ArenaView& A, const void* logits, int32_t T, int32_t
                      out_tok, out_state, out_score, spin ? spin : kSpinLimit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || G == 1) return e;
-  hipLaunchKernelGGL((greedy_fix_kernel<Ld, PER>), dim3(B), dim3(kFixThreads), 0, st, A,
+  hipLaunchKernelGGL((greedy_fix_kernel<Ld, PER>), dim3(B), dim3(fix_threads<PER>()), 0, st, A,
                      static_cast<const TT*>(logits), T, B, stride, G, L, Shape<PER>::W,
                      model_ids, states, out_tok, out_state, out_score);
   return hipGetLastError();
