@@ -61,10 +61,10 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "greedy_chunk_streaming_traffic.js
 KERNELS = {
     "streaming": "greedy short-call kernel (one launch per 16-step chunk)",
     "batched": "segmented greedy kernel + boundary fix-up (one call of 500 steps)",
-    "beam": "beam kernel, one workgroup per stream (one call of 256 steps)",
-    "stress_greedy": "wide-row greedy kernel, one workgroup per time segment, + boundary fix-up "
+    "beam": "row summaries + beam kernel, one workgroup per stream (one call of 256 steps)",
+    "stress_greedy": "row summaries + walk of every stream's rows in parallel segments "
                      "(one call of 256 steps)",
-    "stress_beam": "wide-row beam kernel, one workgroup per stream (one call of 256 steps)",
+    "stress_beam": "row summaries + beam kernel, one workgroup per stream (one call of 256 steps)",
     "lifecycle": "greedy short-call kernel on a registry arena (one launch per 16-step chunk)",
     "variative_streaming": "greedy short-call kernel on variative BPE graphs (one launch per "
                            "16-step chunk)",

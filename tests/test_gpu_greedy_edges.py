@@ -81,6 +81,14 @@ def test_call_lengths(T):
     _check(2305, T, T, "normal", "f32", T)
 
 
+@pytest.mark.parametrize("V1", [65, 1280, 1281, 2048])
+def test_boundary_fix_up_of_narrow_rows(V1):
+    """Calls of several workgroups a stream through the fix-up kernel, on both
+    sides of its change from sixteen waves to eight (1280 values)."""
+    _check(V1, 300, 300, "normal", "f32", 1)
+    _check(V1, 300, 300, "normal", "bf16", 2)
+
+
 def test_call_of_several_pieces():
     """More steps than LDS holds row records for (48 bytes each)."""
     _check(2049, 3500, 3500, "normal", "bf16")
