@@ -165,16 +165,14 @@ def _need(t, n: int, name: str, exact: bool = True) -> None:
         raise ValueError(f"{name} holds {k} elements, needs {'' if exact else 'at least '}{n}")
 
 
-def _buf(t, n: int, dtype, name: str, exact: bool = False) -> int:
-    """_need and _dptr of a required buffer in one call: the step calls of a
-    frame-synchronous decoder are bound by this marshalling."""
+def _fits(t, n: int, dtype, exact: bool = False) -> bool:
+    """Whether _need and _dptr would accept a required buffer: the step calls
+    of a frame-synchronous decoder are bound by this marshalling."""
     if t is None:
-        raise ValueError(f"{name} is required")
+        return False
     k = t.numel()
-    if k < n or (exact and k != n) or not (t.is_cuda and t.dtype == dtype and t.is_contiguous()):
-        _need(t, n, name, exact)
-        _dptr(t, dtype, name)
-    return t.data_ptr()
+    return ((k == n or (k > n and not exact)) and t.is_cuda and t.dtype == dtype
+            and t.is_contiguous())
 
 
 def _stream(stream) -> Optional[int]:
@@ -407,16 +405,22 @@ def tb_boost_step_greedy(arena: Arena, logits, model_ids, states, out_tok, out_s
         raise ValueError("logits steps must be laid out as (t*B + b) * row_stride")
     if row_stride is not None and row_stride != rs:
         raise ValueError(f"row_stride {row_stride} differs from the logits' {rs}")
-    i32, n = torch.int32, T * B
-    mids = _buf(model_ids, B, i32, "model_ids", exact=True)
-    carry = _buf(states, B, i32, "states", exact=True)
-    tok = _buf(out_tok, n, i32, "out_tok")
-    sta = _buf(out_state, n, i32, "out_state")
-    sco = _buf(out_score, n, torch.float32, "out_score")
-    code = LIB.tb_boost_step_greedy(C.byref(arena.arena), _logits_ptr(logits), dt, T, B, rs, mids,
-                                    carry, tok, sta, sco, _stream(stream))
-    if code:
-        _check(code)
+    i32, f32, n = torch.int32, torch.float32, T * B
+    if not (_fits(model_ids, B, i32, True) and _fits(states, B, i32, True)
+            and _fits(out_tok, n, i32) and _fits(out_state, n, i32) and _fits(out_score, n, f32)):
+        # the first fault, sizes before places and types
+        _need(model_ids, B, "model_ids")
+        _need(states, B, "states")
+        outs = (("out_tok", out_tok, i32), ("out_state", out_state, i32),
+                ("out_score", out_score, f32))
+        for name, o, _ in outs:
+            _need(o, n, name, exact=False)
+        _logits_ptr(logits)
+        for name, o, dtype in (("model_ids", model_ids, i32), ("states", states, i32), *outs):
+            _dptr(o, dtype, name)
+    _check(LIB.tb_boost_step_greedy(C.byref(arena.arena), _logits_ptr(logits), dt, T, B, rs,
+                                    model_ids.data_ptr(), states.data_ptr(), out_tok.data_ptr(),
+                                    out_state.data_ptr(), out_score.data_ptr(), _stream(stream)))
 
 
 def tb_boost_step_beam(arena: Arena, logits, model_ids, states, scores, out_tok, out_parent,
