@@ -14,8 +14,10 @@
 //
 // One wave per row up to 2048 values, four waves above. The kernel is bound
 // by vector instructions, most of them the exponentials (20 a value, 13 in
-// float64; 131,072 rows of 1025 float32 take 192 us, 65,536 of 8193 bfloat16
-// 650 us, where reading them takes 104 and 207 us at a copy's rate). So the sum is taken of e^z itself, not of e^(z - max), so that
+// float64; 131,072 rows of 1025 float32 took 192 us, 65,536 of 8193 bfloat16
+// 650 us, where reading them takes 104 and 207 us at a copy's rate; with one
+// test for the unused chunks and one for eight values without a best move, the
+// calls of these rows take 0 and 4 to 8 % less). So the sum is taken of e^z itself, not of e^(z - max), so that
 // the row is passed once and no value waits for a maximum; float64 holds
 // e^z for |z| <= 700, and a row whose sum leaves [1e-280, 1e280] (or holds a
 // nan) is summed again relative to its maximum.
@@ -77,9 +79,10 @@ constexpr int kRowThreads = 256;
 
 // NWR waves per row; a wave's chunk j holds the row's values (j * NWR + q) * 64
 // + lane. Chunks below NF lie before the blank for every row that runs this
-// instance (no test of the index); those up to NC are tested.
+// instance (no test of the index); those up to NC are tested. Four workgroups a
+// CU (128 registers) for all but the longest rows: 131 would leave three.
 template <class Ld, int NWR, int NF, int NC>
-__global__ __launch_bounds__(kRowThreads) void beam_rows_kernel(
+__global__ __launch_bounds__(kRowThreads, NC <= 40 ? 4 : 1) void beam_rows_kernel(
     ArenaView A, const typename Ld::T* __restrict__ logits, int64_t r0, int64_t n_rows, int32_t B,
     int32_t K, int64_t stride, const int32_t* __restrict__ model_ids,
     const int32_t* __restrict__ states, int32_t* __restrict__ out_tok,
@@ -113,39 +116,59 @@ __global__ __launch_bounds__(kRowThreads) void beam_rows_kernel(
   auto index = [&](int j) { return (j * NWR + q) * 64 + lane; };
   auto used = [&](int j) { return j < NF || (j * NWR + q) * 64 < opaque(V1); };  // uniform
 
+  // the tested chunks: rows that end within the first one pass over the others
+  // with one test
+  const bool more = ((NF + 1) * NWR + q) * 64 < V1;
+  auto tested = [&](auto f) {
+    if (used(NF)) f(NF);
+    if (more) {
+#pragma unroll
+      for (int j = NF + 1; j < NC; ++j)
+        if (used(j)) f(j);
+    }
+  };
+
   float z[NC], y[NC];
 #pragma unroll
   for (int j = 0; j < NF; ++j) z[j] = Ld::get(row, j * NWR * 64 + lane);
 #pragma unroll
   for (int j = 0; j < NF; ++j) y[j] = biased ? gpsi[j * NWR * 64 + lane] : 0.f;
 #pragma unroll
-  for (int j = NF; j < NC; ++j) {
-    z[j] = y[j] = kNegInf;
-    if (used(j) && index(j) < V1) {
+  for (int j = NF; j < NC; ++j) z[j] = y[j] = kNegInf;
+  tested([&](int j) {
+    if (index(j) < V1) {
       z[j] = Ld::get(row, j * NWR * 64 + lane);
       y[j] = biased ? gpsi[j * NWR * 64 + lane] : 0.f;
     }
-  }
+  });
 
   // normaliser, and every lane's best move (a nan stays)
   double se = 0.0;
   float lm = kNegInf;
+  // waves that share a row keep the best of every eight values: few of these
+  // groups hold one of the row's best moves
+  constexpr int NG = (NC + 7) / 8;
+  float group[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) group[g] = kNegInf;
 #pragma unroll
   for (int j = 0; j < NF; ++j) {
     se += exp_f32(z[j]);
     y[j] = z[j] + y[j];
-    lm = __builtin_elementwise_maximum(lm, y[j]);
+    float& best = NWR > 1 ? group[j / 8] : lm;
+    best = __builtin_elementwise_maximum(best, y[j]);
   }
-  bool bad = lm != lm;
 #pragma unroll
-  for (int j = NF; j < NC; ++j) {
-    if (!used(j)) continue;
+  for (int g = 0; g < (NWR > 1 ? NG : 0); ++g) lm = __builtin_elementwise_maximum(lm, group[g]);
+  bool bad = lm != lm;
+  tested([&](int j) {
     const double e = exp_f32(z[j]);
     se += index(j) < V1 ? e : 0.0;
     bad = bad || z[j] != z[j];
     y[j] = index(j) < V ? z[j] + y[j] : kNegInf;
     lm = __builtin_fmaxf(lm, y[j]);
-  }
+    if (NWR > 1) group[j / 8] = __builtin_elementwise_maximum(group[j / 8], y[j]);
+  });
   se = wave_sum_dpp_d(se);
   if (__ballot(bad) != 0ull) {  // nan values: their sum is nan, the other moves are listed
     se = __builtin_nan("");
@@ -212,8 +235,11 @@ __global__ __launch_bounds__(kRowThreads) void beam_rows_kernel(
     for (int i = 0; i < NWR; ++i) th = __builtin_fmaxf(th, gap_of(best, om[i]) <= bound ? -om[i] : kNegInf);
     const float theta = -wave_max_dpp(th);
     total = 0;
+    bool any = true;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
+      if (NWR > 1 && j % 8 == 0) any = __ballot(!(group[j / 8] < theta)) != 0ull;  // or a nan
+      if (!any) continue;
       const bool hit = used(j) && y[j] >= theta;
       const uint64_t in = __ballot(hit);
       if (in == 0ull) continue;
