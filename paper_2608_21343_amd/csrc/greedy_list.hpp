@@ -159,16 +159,34 @@ __global__ __launch_bounds__(kRowThreads) void greedy_rows_kernel(
   });
 #pragma unroll
   for (int g = 0; g < NG; ++g) top = __builtin_fmaxf(top, group[g]);
-  // the wave's sum relative to its own maximum (a wave without a finite value
-  // of a row adds nothing: any finite reference will do)
+  // The wave's sum relative to its own maximum. The exponent z log2(e) - mL is
+  // one instruction and off by the rounding of mL alone, so the sum is rescaled
+  // by it. Where that rounding is not small (a wave of nothing but mask values
+  // such as -1e30, where it exceeds every exponent) the maximum is subtracted
+  // first. Largest error of the step scores against float64, 4096 rows of 8193
+  // float32 of deviation 1.5 around 0, 20, 100, 1000: 1.0e-6, 1.5e-6, 4.3e-6,
+  // 3.1e-5 (without the rescaling 1.1e-6, 2.5e-6, 8.5e-6, 6.3e-5).
   zm = wave_max_dpp(zm);
-  const float ref = (NWR > 1 && zm == kNegInf) ? 0.f : zm;
-  const float mL = ref * kLog2e;
+  const float ref = zm == kNegInf ? 0.f : zm;  // no finite value: the terms are 0 (or nan)
+  auto exp_of = [](float x) { return __builtin_amdgcn_exp2f(x * kLog2e); };
   float se = 0.f;
-  auto term = [&](int j) { se += __builtin_amdgcn_exp2f(__builtin_fmaf(z[j], kLog2e, -mL)); };
+  auto sum = [&](auto term) {
 #pragma unroll
-  for (int j = 0; j < NF; ++j) term(j);
-  tested(term);
+    for (int p = 0; p < NP; ++p) {  // a piece at a time: less rounding than one chain
+      float part = 0.f;
+#pragma unroll
+      for (int e = 0; e < PV; ++e) part += term(z[p * PV + e]);
+      se += part;
+    }
+    tested([&](int j) { se += term(z[j]); });
+  };
+  if (__builtin_fabsf(ref) < 8192.f) {  // uniform
+    const float mL = ref * kLog2e;
+    sum([&](float x) { return __builtin_amdgcn_exp2f(__builtin_fmaf(x, kLog2e, -mL)); });
+    se *= __builtin_amdgcn_exp2f(-__builtin_fmaf(ref, kLog2e, -mL));
+  } else {
+    sum([&](float x) { return exp_of(x - ref); });
+  }
   se = wave_sum_dpp(se);
 
   if constexpr (NWR > 1) {
@@ -188,9 +206,8 @@ __global__ __launch_bounds__(kRowThreads) void greedy_rows_kernel(
     se = 0.f;
 #pragma unroll
     for (int i = 0; i < NWR; ++i) {
-      const float mi = g_max[i];
-      if (mi != kNegInf || zm == kNegInf)
-        se += g_sum[i] * __builtin_amdgcn_exp2f((mi - zm) * kLog2e);
+      const float mi = g_max[i];  // -inf: the wave's sum is 0 (or nan, which stays)
+      se += g_sum[i] * (mi == kNegInf ? 0.f : exp_of(mi - zm));
     }
   }
   const float lse = zm + __logf(se);

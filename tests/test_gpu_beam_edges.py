@@ -17,6 +17,7 @@ from tests.gpu_cases import compare_beam, gpu_beam, say
 pytestmark = pytest.mark.gpu
 
 ATOL = 1e-5
+MASKS = {"-1e10": -1e10, "-1e30": -1e30, "lowest": np.finfo(np.float32).min}
 EDGES = [2, 3, 256, 257, 512, 513, 768, 769, 1024, 1025, 1280, 1281, 1536, 1537, 1792, 1793, 2048,
          2049, 3072, 3073, 4096, 4097, 5120, 5121, 6144, 6145, 8192, 8193, 10240, 10241, 16384,
          16385]
@@ -50,8 +51,14 @@ def _run(V1, K, kind, fill, dtype, chunk, T=6):
         keep[..., V] = rng.random(rows.shape[:-1]) < 0.5
         keep[..., 0] |= ~keep.any(-1)
         rows[~keep] = -np.inf
+    elif fill in MASKS:  # 100 tokens kept, all within one wave's share of a row
+        keep = np.zeros(V1, bool)
+        keep[V1 // 2 - V1 // 2 % 256:][:100] = True
+        rows[..., ~keep] = np.float32(MASKS[fill])
     if dtype == "bf16":
         rows = _f32_to_bf16_bits(rows)
+        if fill == "lowest":  # bfloat16's own (the float32 one rounds to -inf)
+            rows[..., ~keep] = 0xff7f
     dec = BoostDecoder(lists, cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
     graphs = {m: oracle.build_graph(lists[m], cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
               for m in (0, 1)}
@@ -87,6 +94,14 @@ def test_wave_layouts(K, kind):
 def test_equal_and_masked_rows(V1, fill, K):
     for kind in ("plain", "stream"):
         _run(V1, K, kind, fill, "f32", 3)
+
+
+@pytest.mark.parametrize("fill", MASKS)
+@pytest.mark.parametrize("V1", [1025, 8193])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_masked_with_a_finite_value(V1, fill, dtype):
+    _run(V1, 4, "plain", fill, dtype, 3)
+    _run(V1, 12, "stream", fill, dtype, 3)
 
 
 @pytest.mark.parametrize("V1", [300, 2305])

@@ -15,6 +15,7 @@ from tests.gpu_cases import compare_greedy, gpu_greedy, say
 pytestmark = pytest.mark.gpu
 
 ATOL = 1e-5
+MASKS = {"-1e10": -1e10, "-1e30": -1e30, "lowest": np.finfo(np.float32).min}
 EDGES = [2049, 3072, 3073, 4096, 4097, 5120, 5121, 6144, 6145, 8192, 8193, 10240, 10241, 16384,
          16385, 32768]
 
@@ -53,8 +54,14 @@ def _case(V1, T, fill, dtype, seed=0):
         keep[..., V] = rng.random(rows.shape[:-1]) < 0.5
         keep[..., 5] |= ~keep.any(-1)
         rows[~keep] = -np.inf
+    elif fill in MASKS:  # 100 tokens kept, all within one wave's share of a row
+        keep = np.zeros(V1, bool)
+        keep[V1 // 2 - V1 // 2 % 256:][:100] = True
+        rows[..., ~keep] = np.float32(MASKS[fill])
     if dtype == "bf16":
         rows = _f32_to_bf16_bits(rows)
+        if fill == "lowest":  # bfloat16's own (the float32 one rounds to -inf)
+            rows[..., ~keep] = 0xff7f
     return cfg, lists, cm, mids, rows
 
 
@@ -100,6 +107,28 @@ def test_call_of_several_pieces():
 def test_equal_and_masked_rows(V1, fill, dtype):
     _check(V1, 12, 12, fill, dtype, 1)
     _check(V1, 12, 12, fill, dtype, 2)
+
+
+@pytest.mark.parametrize("fill", MASKS)
+@pytest.mark.parametrize("V1", [2049, 8193, 12000])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_masked_with_a_finite_value(V1, fill, dtype):
+    """Three of a row's four waves hold nothing but the mask value: their sums
+    weigh nothing, whatever the rounding of such values."""
+    _check(V1, 6, 6, fill, dtype, 1)
+
+
+def test_nan_in_a_wave_without_finite_values():
+    """The score of a row is nan when its only nan lies in a wave's share that
+    holds -inf besides (tokens 256..511 of every 1024 in float32)."""
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    cfg, lists, cm, mids, rows = _case(8193, 3, "normal", "f32")
+    dec = BoostDecoder(lists, cm)
+    rows[1, :, :8192].reshape(4, 8, 4, 256)[:, :, 1] = -np.inf
+    rows[1, 0, 300] = rows[1, 2, 300] = np.nan
+    tok, _, sc, _ = gpu_greedy(dec, to_device_logits(rows), mids, 3)
+    assert np.isnan(sc[1, [0, 2]]).all() and not np.isnan(sc[1, [1, 3]]).any()
+    assert not np.isnan(sc[[0, 2]]).any()
 
 
 @pytest.mark.parametrize("V1", [300, 2305])
