@@ -332,9 +332,9 @@ hipError_t launch_rows_t(const ArenaView& A, const void* logits, int32_t T, int3
                          int64_t stride, const int32_t* model_ids, const int32_t* states,
                          int32_t* out_tok, int32_t* out_parent, int32_t* out_state,
                          float* out_step, float* out_cum, hipStream_t st) {
-  // rows [r0, n_rows) in launches of at most 2^30 workgroups
+  // rows [r0, n_rows) in launches of as many workgroups as one may have
   const int64_t n_rows = (int64_t)T * B * K;
-  constexpr int64_t kPer = (kRowThreads / 64) / NWR, kMost = kPer << 30;
+  constexpr int64_t kPer = (kRowThreads / 64) / NWR, kMost = kPer * most_groups(kRowThreads);
   for (int64_t r0 = 0; r0 < n_rows; r0 += kMost) {
     const int64_t nr = n_rows - r0 < kMost ? n_rows - r0 : kMost;
     hipLaunchKernelGGL((beam_rows_kernel<Ld, NWR, NF, NC>), dim3((uint32_t)((nr + kPer - 1) / kPer)),
@@ -409,10 +409,24 @@ hipError_t launch_step_t(const ArenaView& A, const void* logits, int32_t T, int3
   const Layout l = make_layout(A, T, K, sizeof(typename Ld::T), ROWS,
                                sizeof(Shared<NW * KPW, NW>));
   allow_dynamic_lds(kernel, (size_t)kLdsBytes - sizeof(Shared<NW * KPW, NW>) - 1024);
-  hipLaunchKernelGGL(kernel, dim3(B), dim3(64 * NW), (size_t)l.total, st, A,
-                     static_cast<const typename Ld::T*>(logits), T, B, K, stride, model_ids, states,
-                     scores, out_tok, out_parent, out_state, out_step, out_cum, sa, l);
-  return hipGetLastError();
+  // streams [b0, B) in launches of as many workgroups as one may have
+  constexpr int64_t kMost = most_groups(64 * NW);
+  for (int64_t b0 = 0; b0 < B; b0 += kMost) {
+    const int64_t nb = B - b0 < kMost ? B - b0 : kMost, k0 = b0 * K;
+    StreamArgs s = sa;
+    if constexpr (STREAM) {
+      s.hyps += k0;
+      if (s.tree) s.tree += b0 * sa.cap * 2;
+      s.tree_len += b0;
+    }
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)nb), dim3(64 * NW), (size_t)l.total, st, A,
+                       static_cast<const typename Ld::T*>(logits) + k0 * stride, T, B, K, stride,
+                       model_ids + b0, states + k0, scores + k0, out_tok + k0, out_parent + k0,
+                       out_state + k0, out_step + k0, out_cum + k0, s, l);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Waves: one per slot up to 16, then two slots each. Children per lane: two

@@ -781,9 +781,9 @@ hipError_t launch_t(const ArenaView& A, const void* logits, int32_t T, int32_t B
                     int32_t* out_state, float* out_score, hipStream_t st) {
   typedef typename Ld::T LT;
   const LT* z = static_cast<const LT*>(logits);
-  // rows [r0, n_rows) in launches of at most 2^30 workgroups
+  // rows [r0, n_rows) in launches of as many workgroups as one may have
   const int64_t n_rows = (int64_t)T * B;
-  constexpr int64_t kPer = (kRowThreads / 64) / NWR, kMost = kPer << 30;
+  constexpr int64_t kPer = (kRowThreads / 64) / NWR, kMost = kPer * most_groups(kRowThreads);
   for (int64_t r0 = 0; r0 < n_rows; r0 += kMost) {
     const int64_t nr = n_rows - r0 < kMost ? n_rows - r0 : kMost;
     hipLaunchKernelGGL((greedy_rows_kernel<Ld, NWR, NP, NC>),
@@ -806,12 +806,16 @@ hipError_t launch_t(const ArenaView& A, const void* logits, int32_t T, int32_t B
     int32_t hot = L >= kHotRows ? (room / 16 < 8192 ? room / 16 : 8192) : 0;
     if (hot > A.n_states) hot = (int32_t)A.n_states;
     const int32_t lds = kLdsBytes - room + 16 * hot;
-    hipLaunchKernelGGL(kernel, dim3(B), dim3(64 * waves), (size_t)lds, st, A,
-                       z + (int64_t)t * B * stride, n, B, stride, L, model_ids, states,
-                       out_tok + (int64_t)t * B, out_state + (int64_t)t * B,
-                       out_score + (int64_t)t * B, words, hot, lds);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    // streams [b0, B) in launches of as many workgroups as one may have
+    const int64_t group = most_groups(64 * waves);
+    for (int64_t b0 = 0; b0 < B; b0 += group) {
+      const int64_t nb = B - b0 < group ? B - b0 : group, o = (int64_t)t * B + b0;
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)nb), dim3(64 * waves), (size_t)lds, st, A,
+                         z + o * stride, n, B, stride, L, model_ids + b0, states + b0, out_tok + o,
+                         out_state + o, out_score + o, words, hot, lds);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }

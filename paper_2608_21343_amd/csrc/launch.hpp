@@ -42,6 +42,9 @@ hipError_t launch_greedy_seg(const ArenaView& A, const void* logits, int32_t dty
                              int32_t* states, int32_t* out_tok, int32_t* out_state,
                              float* out_score, hipStream_t st);
 
+// Workgroups a launch may have: a dispatch holds at most 2^32 - 1 work-items.
+constexpr int64_t most_groups(int32_t threads) { return 0xffffffffll / threads; }
+
 // Largest V+1 the step kernels accept: the compiler's limit (the reference
 // kernels' per-class LDS table, 4 B and one bit per class, fits up to it).
 constexpr int32_t kMaxV1 = 32768;
