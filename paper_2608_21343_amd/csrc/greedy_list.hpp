@@ -342,7 +342,7 @@ struct Walk {
 template <class Ld, int NS>
 __device__ __forceinline__ Answer walk_step(const Walk<Ld>& W, const RowRec& R, int32_t t, int32_t x) {
   const ArenaView& A = W.A;
-  const int32_t off = W.off, V = W.V;
+  const int32_t off = W.off, V = W.V, V1 = V + 1;
   const int lane = __lane_id();
   const typename Ld::T* row = W.col + (int64_t)t * W.tstride;
   const int32_t tok1 = __builtin_amdgcn_readfirstlane((int32_t)(R.t12 & 0xffffu));
@@ -419,10 +419,9 @@ __device__ __forceinline__ Answer walk_step(const Walk<Ld>& W, const RowRec& R, 
             const int32_t t2 = (int32_t)(m[g].y & 0xffffu);
             const float z0 = Ld::get(row, t0), z1 = Ld::get(row, t1), z2 = Ld::get(row, t2);
             const float k0 = z0 + py[g], k1 = z1 + py[g], k2 = z2 + py[g];
-            kb[g] = k0;
-            tk[g] = t0;
-            zk[g] = z0;
-            if (k1 > kb[g]) { kb[g] = k1; tk[g] = t1; zk[g] = z1; }  // members ascend: ties keep the lower
+            // members ascend: ties keep the lower; a nan is passed over
+            if (k0 > kb[g]) { kb[g] = k0; tk[g] = t0; zk[g] = z0; }
+            if (k1 > kb[g]) { kb[g] = k1; tk[g] = t1; zk[g] = z1; }
             if (k2 > kb[g]) { kb[g] = k2; tk[g] = t2; zk[g] = z2; }
           }
           hit = hit || lab[g] == R.cls1;
@@ -594,7 +593,7 @@ __device__ __forceinline__ Answer walk_step(const Walk<Ld>& W, const RowRec& R, 
   a.ns = x;
   a.z = zb;
   a.b = 0.f;
-  float k = bk;  // the blank keeps the state
+  float k = bk > kNegInf ? bk : kNegInf;  // the blank keeps the state (a nan never wins)
   int32_t v = V;
   if (better(ok, ot, k, v)) {
     k = ok;
@@ -612,9 +611,25 @@ __device__ __forceinline__ Answer walk_step(const Walk<Ld>& W, const RowRec& R, 
     k = rk;
   }
   if (__builtin_amdgcn_readfirstlane((int32_t)(k == kNegInf))) {
-    // every key is -inf: the lowest token, at its own move
-    const int32_t c = sload(A.class_map);
-    int32_t ns = sload(W.gdst);
+    // no key is above -inf: the lowest that is no nan (the first token when all
+    // are), at its own move
+    int32_t v0 = V1;
+    for (int32_t i = 0; i < V1 && v0 == V1; i += 64) {
+      const bool in = i + lane < V1;
+      const float zi = Ld::get(row, in ? i + lane : 0);
+      const uint64_t is = __ballot(in && zi == zi);
+      if (is != 0ull) v0 = i + (int32_t)__builtin_ctzll(is);
+    }
+    if (v0 == V) {
+      a.tok = V;
+      a.ns = x;
+      a.z = zb;
+      a.b = 0.f;
+      return a;
+    }
+    if (v0 == V1) v0 = 0;
+    const int32_t c = sload(A.class_map + v0);
+    int32_t ns = sload(W.gdst + v0);
     bool found = false;
     for (int32_t s = x; s != 0 && c >= 0 && !found; s = sload(A.link + off + s)) {
       const int32_t c0 = sload(A.first_child + off + s), cn = sload(A.n_child + off + s);
@@ -624,9 +639,9 @@ __device__ __forceinline__ Answer walk_step(const Walk<Ld>& W, const RowRec& R, 
         if (found) ns = c0 + j0 + (int32_t)__builtin_ctzll(at);
       }
     }
-    a.tok = 0;
+    a.tok = v0;
     a.ns = ns;
-    a.z = Ld::get(row, 0);
+    a.z = Ld::get(row, v0);
     a.b = sload(A.psi + off + ns) - phi;
   }
   return a;
@@ -683,11 +698,16 @@ __global__ __launch_bounds__(kWalkThreads) void greedy_walk_kernel(
       r.y1 = r.z1 + r.psi1;
     }
     if (!biased) {  // the best of the tokens and the blank
-      const bool blank = !better(r.y1, t1, r.zb, V);
-      const bool none = r.y1 == kNegInf && r.zb == kNegInf;  // the lowest token
-      out_tok[o] = none ? 0 : (blank ? V : t1);
+      int32_t v = better(r.zb, V, r.y1, t1) ? V : t1;
+      float z = v == V ? r.zb : r.z1;
+      if (!(r.y1 > kNegInf || r.zb > kNegInf)) {  // as walk_step
+        for (v = 0; v < V && Ld::get(row, v) != Ld::get(row, v); ++v) {}
+        if (v == V && r.zb != r.zb) v = 0;  // nothing but nan
+        z = Ld::get(row, v);
+      }
+      out_tok[o] = v;
       out_state[o] = fixed;
-      out_score[o] = (blank ? r.zb : r.z1) - r.lse;
+      out_score[o] = z - r.lse;
     }
     r.tok = 0;
     r.ns = 0;

@@ -118,6 +118,50 @@ def test_rows_masked_with_a_finite_value(V1, fill, dtype):
     _check(V1, 6, 6, fill, dtype, 1)
 
 
+@pytest.mark.parametrize("V1,dtype,chunk", [(2305, "f32", 14), (2305, "bf16", 1), (8193, "f32", 3),
+                                            (8193, "bf16", 14)])
+@pytest.mark.parametrize("seed", [1, 2])
+def test_rows_of_nan_and_of_no_finite_value(V1, dtype, chunk, seed):
+    """A nan never wins: tokens and states are the oracle's for the same rows
+    with -inf in its place. Among rows without a finite key the lowest token
+    that is no nan is taken (the blank after the tokens), at its own move. The
+    scores of such rows, and of rows that hold a nan, are nan."""
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    from workloads.synth import _f32_to_bf16_bits
+    T, V = 14, V1 - 1
+    cfg, lists, cm, mids, rows = _case(V1, T, "normal", "f32", seed)
+    say(f"[greedy edge] nan and -inf rows V+1={V1} {dtype} chunk={chunk} seed={seed}")
+    n = V // 7 if seed % 2 else V // 6  # first members of the classes
+    rows[2, :, V] = np.nan
+    rows[4, :, :n] = np.nan
+    rows[4, :, n:2 * n] += np.float32(3.0)
+    rows[5, :, 0] = np.nan  # the blank is the best
+    rows[5, :, V] = 20.0
+    rows[6] = -np.inf
+    rows[8, :, :V] = -np.inf
+    rows[8, :, :5] = np.nan
+    rows[8, :, V] = -np.inf
+    rows[9] = np.nan
+    rows[11] = np.nan
+    rows[11, :, V] = -np.inf
+    want = np.where(np.isnan(rows), np.float32(-np.inf), rows)
+    want[8, :, 5] = want[11, :, V] = 0.0  # the rows' lowest entries that are no nan
+    if dtype == "bf16":
+        rows, want = _f32_to_bf16_bits(rows), _f32_to_bf16_bits(want)
+    dec = BoostDecoder(lists, cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+    graphs = {m: oracle.build_graph(lists[m], cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+              for m in (0, 1, 3)}
+    st0 = np.where(mids >= 0, 0, -1).astype(np.int32)
+    got = gpu_greedy(dec, to_device_logits(rows), mids, chunk)
+    with np.errstate(invalid="ignore"):
+        ref = oracle.greedy_decode(graphs, mids, want, st0)
+    none = np.isin(np.arange(T), [2, 4, 5, 6, 8, 9, 11])
+    assert np.isnan(got[2][none]).all()
+    compare_greedy([a[~none] for a in got[:3]], [a[~none] for a in ref[:3]], range(cfg.B), ATOL)
+    assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+    assert (got[1][[6, 8], :2] >= 0).all() and (ref[1][:, [0, 1, 3]] > 0).any()
+
+
 def test_nan_in_a_wave_without_finite_values():
     """The score of a row is nan when its only nan lies in a wave's share that
     holds -inf besides (tokens 256..511 of every 1024 in float32)."""
