@@ -1015,6 +1015,7 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
         int32_t bc = INT_MAX, bd = fixed;
         auto offer = [&](bool p, int32_t k, int32_t v, float val, int32_t dst, float step) {
           const int32_t code = (k << 16) | v;
+          if (p && code == 0) S.bound[0] = dst;  // its place when no candidate is left
           const bool after = j == 0 || val < pvl || (val == pvl && code > pcode);
           if (p && after && better(val, code, bv, bc)) {
             bv = val;
@@ -1087,10 +1088,10 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
         const int32_t gd = rl(rd, gl);
         const float gs = rlf(rs, gl);
         if (lane == j) {
-          // none left: only reachable with nan logits
+          // none left (nan values only): slot 0 by its first token, no score
           w_code = gc == INT_MAX ? ~0u : ~(uint32_t)gc;
-          w_dst = gc == INT_MAX ? (biased ? 0 : fixed) : gd;
-          w_step = gs;
+          w_dst = gc == INT_MAX ? S.bound[0] : gd;
+          w_step = gc == INT_MAX ? __builtin_nanf("") : gs;
           w_val = gv;
         }
         pvl = gv;

@@ -126,3 +126,43 @@ def test_nan_row_leaves_other_streams(V1):
         assert np.array_equal(a[:, [0, 2]], b[:, [0, 2]])
     tok, par = (np.asarray(got[i]).reshape(-1, 3, 5) for i in (0, 1))
     assert tok.min() >= 0 and tok.max() <= cfg.V and par.min() >= 0 and par.max() < 5
+
+
+@pytest.mark.parametrize("V1", [300, 2305])
+@pytest.mark.parametrize("K", [1, 3, 8, 12, 32])
+def test_steps_without_a_candidate(V1, K):
+    """A step whose rows are all nan or all -inf leaves no candidate: every slot
+    takes the first token from slot 0 and its state, with score -inf, as the
+    reference kernel does, and the steps after it go on from there."""
+    from paper_2608_21343_amd import capi
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    say(f"[beam edge] no candidate V+1={V1} K={K}")
+    cfg = W.Config(8900 + V1, "none", B=4, K=K, V=V1 - 1, T=9, chunk=9, dtype="f32", n_phrases=20,
+                   len_lo=2, len_hi=4, token_dist="zipf", zipf_s=1.1, logit_std=1.0,
+                   blank_offset=0.0, n_case=V1 // 6)
+    lists = [list(p) for p in W.phrases(cfg)]
+    first = int(lists[0][0][0])
+    lists[0].append(np.array([first, 0, 3], np.int32))  # the first token continues a phrase
+    rows = np.array(W.logits(cfg))
+    mids = np.array([0, 1, -1, 3], np.int32)
+    rows[2, :, :, first] += 9.0
+    rows[3] = np.nan
+    rows[4, 0] = rows[6, 1] = -np.inf
+    rows[6, 3, 0, 5] = np.nan
+    dec = BoostDecoder(lists, W.class_map(cfg))
+    dev = to_device_logits(rows)
+
+    def run(kernel):
+        with capi.kernels(beam=kernel):
+            carry = dec.start_beam_stream(mids, K, 64)
+            out = [np.asarray(o.cpu()) for o in dec.beam_stream(dev, carry)]
+            return list(gpu_beam(dec, dev, mids, 9)), out + [
+                np.asarray(o.cpu()) for o in (carry.states, carry.scores, carry.hyps, carry.tree,
+                                              carry.tree_len)]
+
+    for got, want in zip(run(capi.BEAM_AUTO), run(capi.BEAM_REF)):
+        assert (want[0][3] == 0).all() and (want[4][3] == -np.inf).all()
+        assert np.isnan(want[3][3]).all()
+        for i, (a, b) in enumerate(zip(got, want)):
+            assert np.array_equal(a, b, equal_nan=a.dtype == np.float32) if i != 3 else \
+                np.allclose(a, b, rtol=0, atol=ATOL, equal_nan=True), i
