@@ -327,6 +327,9 @@ int tb_init_states(const tb_arena* a, int32_t B, int32_t K, const int32_t* model
  *   out_tok, out_state  device int32[T*B];  out_score device float[T*B]
  *
  * T = 0 is a no-op that touches no buffer (logits and outputs may be NULL).
+ * In calls of one step outputs may share memory with one another and with the
+ * carry (out_state may be states); at V+1 > 2048 they then take the reference
+ * kernel, which is slower.
  * Results do not depend on how the T steps are split into calls. Log-softmax here is float32 (|error| well below 1e-5); selection
  * does not depend on it.
  */
@@ -352,6 +355,8 @@ int tb_boost_step_greedy(const tb_arena* a, const void* logits, int32_t dtype, i
  *   out_tok, out_parent, out_state  device int32[T*B*K]
  *   out_step (the step's log-prob plus boost), out_cum (S)  device float[T*B*K]
  *
+ * In calls of one step outputs may share memory with one another and with the
+ * carry; they then take the reference kernel, which is slower.
  * T = 0 is a no-op that touches no buffer (they may be NULL).
  */
 enum { TB_MAX_BEAM = 32 }; /* the paper's beam search uses 32 hypotheses */

@@ -435,12 +435,29 @@ static hipError_t launch_list(const ArenaView& A, const void* logits, int32_t dt
               out_state, out_step, out_cum, sa, st);
 }
 
-// The reference kernel serves only tests, through tb_debug_select_kernels.
+// Whether a call's outputs share memory with one another or with its carry.
+static bool shared(int32_t T, int32_t B, int32_t K, const int32_t* model_ids, const int32_t* states,
+                   const float* scores, const int32_t* out_tok, const int32_t* out_parent,
+                   const int32_t* out_state, const float* out_step, const float* out_cum,
+                   StreamArgs sa) {
+  const int64_t n = 4 * (int64_t)B, k = n * K, o = T * k;
+  const Span spans[] = {{out_tok, o}, {out_parent, o}, {out_state, o}, {out_step, o}, {out_cum, o},
+                        {states, k}, {scores, k}, {model_ids, n},
+                        {sa.hyps, sa.hyps ? k / 4 * (int64_t)sizeof(tb_hyp) : 0},
+                        {sa.tree, sa.tree ? 2 * n * sa.cap : 0},
+                        {sa.tree_len, sa.tree_len ? n : 0}};
+  return outputs_shared(spans, 5);
+}
+
+// The reference kernel serves tests, through tb_debug_select_kernels, and calls
+// whose outputs share memory.
 hipError_t launch_beam(const ArenaView& A, const void* logits, int32_t dtype, int32_t T, int32_t B,
                        int32_t K, int64_t row_stride, const int32_t* model_ids, int32_t* states,
                        float* scores, int32_t* out_tok, int32_t* out_parent, int32_t* out_state,
                        float* out_step, float* out_cum, hipStream_t st) {
-  if (debug_beam_kernel() != kBeamRef)
+  if (debug_beam_kernel() != kBeamRef &&
+      !shared(T, B, K, model_ids, states, scores, out_tok, out_parent, out_state, out_step, out_cum,
+              StreamArgs{}))
     return launch_list(A, logits, dtype, T, B, K, row_stride, model_ids, states, scores, out_tok,
                        out_parent, out_state, out_step, out_cum, false, StreamArgs{}, st);
   if (dtype == TB_F32)
@@ -464,7 +481,9 @@ hipError_t launch_beam_stream(const ArenaView& A, const void* logits, int32_t dt
   sa.cap = tree_cap;
   sa.tree_len = tree_len;
   sa.recombine = recombine;
-  if (debug_beam_kernel() != kBeamRef)
+  if (debug_beam_kernel() != kBeamRef &&
+      !shared(T, B, K, model_ids, states, scores, out_tok, out_parent, out_state, out_step, out_cum,
+              sa))
     return launch_list(A, logits, dtype, T, B, K, row_stride, model_ids, states, scores, out_tok,
                        out_parent, out_state, out_step, out_cum, true, sa, st);
   if (dtype == TB_F32)

@@ -60,11 +60,11 @@ namespace tbias {
 
 // Carry of the streaming beam (tb_boost_step_beam_stream); unused otherwise.
 struct StreamArgs {
-  tb_hyp* hyps;   // [B*K]
-  int32_t* tree;  // [B*cap*2] (label, parent record)
-  int32_t cap;
-  int32_t* tree_len;  // [B]
-  int32_t recombine;
+  tb_hyp* hyps = nullptr;   // [B*K]
+  int32_t* tree = nullptr;  // [B*cap*2] (label, parent record)
+  int32_t cap = 0;
+  int32_t* tree_len = nullptr;  // [B]
+  int32_t recombine = 0;
 };
 
 namespace blist {

@@ -1,5 +1,6 @@
 // Boosted greedy step: the dispatch, and the reference kernel, one workgroup
-// per stream, that tests compare the others with.
+// per stream, that tests compare the others with and that serves wide rows whose
+// outputs share memory.
 //
 // Per step the workgroup (Sec. II-B fused scoring operation):
 //   1. reads the stream's logit row and forms the log-softmax normaliser;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(kThreads) void greedy_ref_kernel(
     block_argmax(bk, bi, redf, redi);
 
     if (tid == 0) {
-      const int32_t v = bi;
+      const int32_t v = bi < V1 ? bi : 0;  // no key: only with nan logits
       int32_t ns;
       float bst = 0.f;
       if (mode == 1) {
@@ -176,9 +177,13 @@ hipError_t launch_greedy(const ArenaView& A, const void* logits, int32_t dtype, 
     if (A.V1 <= 64 * 32)
       return launch_greedy_seg(A, logits, dtype, T, B, row_stride, model_ids, states, out_tok,
                                out_state, out_score, st);
-    const glist::Launch f =
-        dtype == TB_F32 ? glist::launcher_f32(A.V1) : glist::launcher_bf16(A.V1);
-    return f(A, logits, T, B, row_stride, model_ids, states, out_tok, out_state, out_score, st);
+    const int64_t n = 4 * (int64_t)B, o = T * n;
+    const Span spans[] = {{out_tok, o}, {out_state, o}, {out_score, o}, {states, n}, {model_ids, n}};
+    if (!outputs_shared(spans, 3)) {
+      const glist::Launch f =
+          dtype == TB_F32 ? glist::launcher_f32(A.V1) : glist::launcher_bf16(A.V1);
+      return f(A, logits, T, B, row_stride, model_ids, states, out_tok, out_state, out_score, st);
+    }
   }
   const size_t lds = ref_table_bytes(A.V1 - 1);
   if (dtype == TB_F32) {

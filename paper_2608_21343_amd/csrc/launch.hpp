@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 #include "device.hpp"
 
 namespace tbias {
@@ -44,6 +46,28 @@ hipError_t launch_greedy_seg(const ArenaView& A, const void* logits, int32_t dty
 
 // Workgroups a launch may have: a dispatch holds at most 2^32 - 1 work-items.
 constexpr int64_t most_groups(int32_t threads) { return 0xffffffffll / threads; }
+
+// Byte ranges of a call's buffers.
+struct Span {
+  const void* p;
+  int64_t bytes;
+};
+inline bool overlap(const Span& a, const Span& b) {
+  const uintptr_t x = (uintptr_t)a.p, y = (uintptr_t)b.p;
+  return x < y + (uint64_t)b.bytes && y < x + (uint64_t)a.bytes;
+}
+// Whether one of the first n_out spans (a call's outputs) shares memory with
+// another span. The list kernels keep row summaries in the outputs, so such a
+// call (a frame-synchronous one that lets out_state be states, or one buffer for
+// two outputs that nobody reads) takes the reference kernel, which writes a
+// step's outputs after it has read what the step needs.
+template <int N>
+inline bool outputs_shared(const Span (&s)[N], int n_out) {
+  for (int i = 0; i < n_out; ++i)
+    for (int j = i + 1; j < N; ++j)
+      if (overlap(s[i], s[j])) return true;
+  return false;
+}
 
 // Largest V+1 the step kernels accept: the compiler's limit (the reference
 // kernels' per-class LDS table, 4 B and one bit per class, fits up to it).
