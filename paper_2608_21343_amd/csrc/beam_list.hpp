@@ -27,7 +27,8 @@
 //     the chain's children (deeper states first: a child whose class a deeper
 //     chain state also has is dropped) and of the listed root moves whose
 //     class no child has, and the blank c + (z[V] + phi(s)). The values of
-//     the listed moves and of the blank are posted to the other waves.
+//     the listed moves and of the blank are posted to the other waves; a listed
+//     token whose class a child has is posted with that child's value.
 //  2. a bound that at least K posted candidates reach (every wave finds the
 //     same one by bisection over the gap to the best posted candidate,
 //     rounded to 4 bits of mantissa: 9 ballots per posted register). The
@@ -455,8 +456,9 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
     };
     // every override member of state s, level by level (deepest first): the
     // class bitmap mk is cleared first and holds the overridden classes
-    // afterwards. f(valid, token, child, psi) runs with all lanes.
-    auto walk = [&](int32_t s, uint32_t* mk, auto f) {
+    // afterwards. f(valid, token, child, psi) runs with all lanes, and before it
+    // g(valid, class, psi) for every child that counts.
+    auto walk_children = [&](int32_t s, uint32_t* mk, auto f, auto g) {
       mark_clear(mk);
       if (!biased || s == 0) return;
       Graph::State st = G.state(s);
@@ -483,6 +485,7 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
               nm = A.cls_ptr[lab + 1] - q0;
             }
           }
+          g(take, lab, py);
           for (int32_t i = 0; __ballot(i < nm) != 0ull; ++i) {
             int32_t tk = 0;
             if (i < nm) {
@@ -498,6 +501,10 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
         if (st.link == 0) break;
         st = G.state(st.link);
       }
+    };
+
+    auto walk = [&](int32_t s, uint32_t* mk, auto f) {
+      walk_children(s, mk, f, [](bool, int32_t, float) {});
     };
 
     // ---- 1. candidates
@@ -568,6 +575,7 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
       h.on = 0u;
       float top = kNegInf;
       bool over = false;
+      float opsi = kNegInf;  // psi of the child that has the listed move's class
       if (biased && h.s != 0) {  // the root's children are the root moves
         Graph::State st = G.state(h.s);
         h.phi = st.phi;
@@ -638,16 +646,26 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
               }
             }
             // the listed moves whose class a child has
-            uint32_t om = 0u;
+            // and the psi of the deepest such child (the first): the move's
+            // token is a candidate through it
 #pragma unroll
             for (int q = 0; q < kList; ++q) {
               const int32_t cq = rl(h.cls, q);
               bool hit = false;
 #pragma unroll
               for (int g = 0; g < NS; ++g) hit = hit || lab[g] == cq;
-              om |= __ballot(hit) != 0ull ? 1u << q : 0u;
+              if (__ballot(hit) == 0ull) continue;
+              float pq = 0.f;
+#pragma unroll
+              for (int g = NS - 1; g >= 0; --g) {
+                const uint64_t at = __ballot(lab[g] == cq);
+                if (at != 0ull) pq = rlf(h.py[g], (int32_t)__builtin_ctzll(at));
+              }
+              if (lane == q) {
+                over = true;
+                opsi = pq;
+              }
             }
-            over = ((om >> lane) & 1u) != 0u && lane < kList;
             // drop the children that a deeper state's child shadows
             for (int32_t j = 0; j < deep; ++j) {
               const int32_t cj = rl(lab[0], j);
@@ -660,7 +678,19 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
           }
         }
         if (h.big) {
-          walk(h.s, marks_of[i], [](bool, int32_t, int32_t, float) {});
+          walk_children(h.s, marks_of[i], [](bool, int32_t, int32_t, float) {},
+                        [&](bool take, int32_t lab, float py) {
+                          bool hit = false;
+#pragma unroll
+                          for (int q = 0; q < kList; ++q) hit = hit || lab == rl(h.cls, q);
+                          if (__ballot(take && hit) == 0ull) return;
+                          for (int32_t q = 0; q < kList; ++q) {
+                            const uint64_t at = __ballot(take && lab == rl(h.cls, q));
+                            if (at == 0ull) continue;
+                            const float pq = rlf(py, (int32_t)__builtin_ctzll(at));
+                            if (lane == q) opsi = pq;
+                          }
+                        });
           over = h.cls >= 0 && lane < kList && marked(marks_of[i], h.cls);
         }
       }
@@ -669,7 +699,12 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
       h.lv = kNegInf;
       if (lane < kList && h.tok >= 0 && !over) h.lv = h.c + (h.z + h.rpsi);
       if (lane == kList) h.lv = h.c + (h.z + h.phi);
-      float post = h.lv;
+      // A listed token whose class a child has is a candidate with the child's
+      // psi. Where most classes have one (many phrases over few tokens) the
+      // blanks alone would leave a weak bound, which most of the row reaches (100
+      // streams, 2 hypotheses, 1000 phrases over 200 tokens, calls of 16 steps:
+      // 154 us without, 86 us with it; 32 hypotheses of 1000 tokens 1680 and 550).
+      float post = over && h.tok >= 0 ? h.c + (h.z + opsi) : h.lv;
       if constexpr (STREAM) {
         if (lane == 0) {
           S.c[k] = h.c;

@@ -571,13 +571,23 @@ __device__ __forceinline__ Answer walk_step(const Walk<Ld>& W, const RowRec& R, 
         }
         float bv = kNegInf;
         int32_t bt = INT_MAX;
-        for (int32_t v = lane; v < V; v += 64) {
-          const float k = Ld::get(row, v) + gload(W.gpsi + v);
-          const int32_t c = gload(A.class_map + v);
-          const bool mk = c >= 0 && ((W.marks[c >> 5] >> (c & 31)) & 1u);
-          if (!mk && k > bv) {  // v ascends: ties keep the lower
-            bv = k;
-            bt = v;
+        constexpr int SC = 8;  // chunks whose loads are in flight together
+        for (int32_t v0 = 0; v0 < V; v0 += 64 * SC) {
+          float kc[SC];
+          int32_t cc[SC];
+#pragma unroll
+          for (int q = 0; q < SC; ++q) {
+            const int32_t v = min(v0 + 64 * q + lane, V);
+            kc[q] = Ld::get(row, v) + gload(W.gpsi + v);
+            cc[q] = gload(A.class_map + v);
+          }
+#pragma unroll
+          for (int q = 0; q < SC; ++q) {
+            const int32_t v = v0 + 64 * q + lane, c = cc[q];
+            if (v < V && kc[q] > bv && !(c >= 0 && ((W.marks[c >> 5] >> (c & 31)) & 1u))) {
+              bv = kc[q];  // v ascends: ties keep the lower
+              bt = v;
+            }
           }
         }
         wave_argmax_dpp(bv, bt, rk, rt);

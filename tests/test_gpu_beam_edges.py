@@ -96,6 +96,40 @@ def test_equal_and_masked_rows(V1, fill, K):
         _run(V1, K, kind, fill, "f32", 3)
 
 
+@pytest.mark.parametrize("V1,phrases,members", [(61, 600, 3), (201, 900, 3), (201, 900, 5),
+                                                (301, 3000, 3), (2101, 6000, 3)])
+@pytest.mark.parametrize("K", [1, 2, 4, 7, 12, 32])
+def test_children_for_most_classes(V1, phrases, members, K):
+    """Many phrases over few tokens: most of a row's best root moves are
+    overridden, by children held one per lane and by larger sets."""
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    say(f"[beam edge] dense lists V+1={V1} phrases={phrases} members={members} K={K}")
+    V, T = V1 - 1, 10
+    cfg = W.Config(8400 + V1 + K, "dense", B=3, K=K, V=V, T=T, chunk=T, dtype="f32",
+                   n_phrases=phrases, len_lo=1, len_hi=6, token_dist="zipf", zipf_s=1.1,
+                   logit_std=1.5, blank_offset=0.5, n_case=V // 9)
+    lists, cm = W.phrases(cfg), W.class_map(cfg)
+    if members == 5:
+        n = V // 7
+        cm = np.arange(V + 1, dtype=np.int32)
+        for k in range(1, 5):
+            cm[k * n:(k + 1) * n] = np.arange(n)
+        cm[V] = -1
+    rows = np.array(W.logits(cfg))
+    mids = np.array([0, 1, -1], np.int32)
+    dec = BoostDecoder(lists, cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+    graphs = {m: oracle.build_graph(lists[m], cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+              for m in (0, 1)}
+    dev = to_device_logits(rows)
+    st0, S0 = oracle.init_carry(mids, K)
+    compare_beam(gpu_beam(dec, dev, mids, 5), oracle.beam_decode(graphs, mids, rows, st0, S0),
+                 range(3), ATOL)
+    carry, want = dec.start_beam_stream(mids, K, 64), oracle.init_stream_carry(mids, K)
+    got = [o.cpu().numpy() for o in dec.beam_stream(dev, carry)]
+    compare_beam(got, oracle.beam_decode_stream(graphs, mids, rows, want, tree_cap=64), range(3),
+                 ATOL)
+
+
 @pytest.mark.parametrize("fill", MASKS)
 @pytest.mark.parametrize("V1", [1025, 8193])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
