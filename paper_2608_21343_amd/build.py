@@ -19,7 +19,7 @@ ROCM = Path(os.environ.get("ROCM_PATH", "/opt/rocm"))
 
 HIP_SOURCES = ["capi.hip", "greedy.hip", "greedy_seg.hip",
                "greedy_seg_1_8.hip", "greedy_seg_9_16.hip", "greedy_seg_17_24.hip",
-               "greedy_seg_25_32.hip", "greedy_list_f32.hip",
+               "greedy_seg_25_32.hip", "greedy_wide.hip", "greedy_list_f32.hip",
                "greedy_list_bf16.hip", "beam.hip", "beam_list_f32.hip",
                "beam_list_bf16.hip", "state.hip", "registry.hip"]
 CXX_SOURCES = ["compiler.cpp", "variative.cpp", "cache.cpp", "errors.cpp"]

@@ -1043,6 +1043,7 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
       }
     } else {
       // K rounds of an argmax over every candidate after the last one taken
+      constexpr int32_t kRootMove = INT_MIN;  // the token's root move, looked up for the best
       float pvl = 0.f;
       int32_t pcode = -1;
       for (int32_t j = 0; j < K; ++j) {
@@ -1050,7 +1051,7 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
         int32_t bc = INT_MAX, bd = fixed;
         auto offer = [&](bool p, int32_t k, int32_t v, float val, int32_t dst, float step) {
           const int32_t code = (k << 16) | v;
-          if (p && code == 0) S.bound[0] = dst;  // its place when no candidate is left
+          if (j == 0 && p && code == 0) S.bound[0] = dst == kRootMove ? gdst[0] : dst;  // its place when no candidate is left
           const bool after = j == 0 || val < pvl || (val == pvl && code > pcode);
           if (p && after && better(val, code, bv, bc)) {
             bv = val;
@@ -1081,28 +1082,32 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
                     (zv - h.lse) + (biased ? px - h.phi : 0.f));
             }
           }
-          for (int32_t v0 = 0; v0 < V; v0 += 64) {
-            const int32_t v = v0 + lane;
-            bool p = v < V;
-            float z = kNegInf, ps = 0.f;
-            int32_t dst = fixed;
-            if (p) {
-              z = zat(i, v);
-              if (biased) {
-                ps = gpsi[v];
-                dst = gdst[v];
-                const int32_t cl = A.class_map[v];
-                p = !(cl >= 0 && marked(marks_of[i], cl));
-              }
+          constexpr int SC = 8;  // chunks whose loads are in flight together
+          for (int32_t v0 = 0; v0 < V; v0 += 64 * SC) {
+            float pc[SC];
+            int32_t cc[SC];
+#pragma unroll
+            for (int q = 0; q < SC; ++q) {
+              const int32_t v = min(v0 + 64 * q + lane, V);
+              pc[q] = biased ? gload(gpsi + v) : 0.f;
+              cc[q] = biased ? gload(A.class_map + v) : -1;
             }
-            if (STREAM && pair_x[i]) p = p && !patched(i, v);
-            offer(p, k, v, h.c + (z + ps), dst, (z - h.lse) + (biased ? ps - h.phi : 0.f));
+#pragma unroll
+            for (int q = 0; q < SC; ++q) {
+              const int32_t v = v0 + 64 * q + lane;
+              bool p = v < V && !(cc[q] >= 0 && marked(marks_of[i], cc[q]));
+              if (STREAM && pair_x[i]) p = p && !patched(i, v);
+              const float z = zat(i, min(v, V));
+              offer(p, k, v, h.c + (z + pc[q]), biased ? kRootMove : fixed,
+                    (z - h.lse) + (biased ? pc[q] - h.phi : 0.f));
+            }
           }
         }
         float wv;
         int32_t wc;
         const int32_t wl = wave_argmax_dpp(bv, bc, wv, wc);
-        const int32_t wd = rl(bd, wl);
+        int32_t wd = rl(bd, wl);
+        if (wd == kRootMove) wd = sload(gdst + (wc & 0xffff));
         const float ws = rlf(bstep, wl);
         const int rp = j & 1;
         if (lane == 0) {

@@ -177,6 +177,9 @@ hipError_t launch_greedy(const ArenaView& A, const void* logits, int32_t dtype, 
     if (A.V1 <= 64 * 32)
       return launch_greedy_seg(A, logits, dtype, T, B, row_stride, model_ids, states, out_tok,
                                out_state, out_score, st);
+    const hipError_t e = launch_greedy_wide(A, logits, dtype, T, B, row_stride, model_ids, states,
+                                            out_tok, out_state, out_score, st);
+    if (e != hipErrorNotSupported) return e;
     const int64_t n = 4 * (int64_t)B, o = T * n;
     const Span spans[] = {{out_tok, o}, {out_state, o}, {out_score, o}, {states, n}, {model_ids, n}};
     if (!outputs_shared(spans, 3)) {

@@ -571,7 +571,7 @@ __device__ __forceinline__ Answer walk_step(const Walk<Ld>& W, const RowRec& R, 
         }
         float bv = kNegInf;
         int32_t bt = INT_MAX;
-        constexpr int SC = 8;  // chunks whose loads are in flight together
+        constexpr int SC = 16;  // chunks whose loads are in flight together
         for (int32_t v0 = 0; v0 < V; v0 += 64 * SC) {
           float kc[SC];
           int32_t cc[SC];

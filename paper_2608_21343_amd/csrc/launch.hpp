@@ -44,6 +44,13 @@ hipError_t launch_greedy_seg(const ArenaView& A, const void* logits, int32_t dty
                              int32_t* states, int32_t* out_tok, int32_t* out_state,
                              float* out_score, hipStream_t st);
 
+// Calls of few steps over rows of more than 2048 values; hipErrorNotSupported
+// for calls that row summaries and walk (greedy_list.hpp) serve better.
+hipError_t launch_greedy_wide(const ArenaView& A, const void* logits, int32_t dtype, int32_t T,
+                              int32_t B, int64_t row_stride, const int32_t* model_ids,
+                              int32_t* states, int32_t* out_tok, int32_t* out_state,
+                              float* out_score, hipStream_t st);
+
 // Workgroups a launch may have: a dispatch holds at most 2^32 - 1 work-items.
 constexpr int64_t most_groups(int32_t threads) { return 0xffffffffll / threads; }
 

@@ -88,6 +88,30 @@ def test_call_lengths(T):
     _check(2305, T, T, "normal", "f32", T)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V1", [2049, 3072, 3073, 4096, 4097, 6144, 6145, 8448, 8449, 10496, 10497])
+def test_calls_of_few_steps(V1, dtype):
+    """Calls of one to seven steps on both sides of the line between the kernel
+    that scores every token and the row summaries, which lies where the rows'
+    instance, the type and the streams (from 128 and 256 on) set it. The streams
+    repeat four streams."""
+    from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
+    T = 14
+    cfg, lists, cm, mids, rows = _case(V1, T, "normal", dtype, V1 % 2)
+    dec = BoostDecoder(lists, cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+    graphs = {m: oracle.build_graph(lists[m], cm, token_w=cfg.token_w, end_bonus=cfg.end_bonus)
+              for m in (0, 1, 3)}
+    st0 = np.where(mids >= 0, 0, -1).astype(np.int32)
+    ref = oracle.greedy_decode(graphs, mids, rows, st0)
+    dev = to_device_logits(rows)
+    for B, chunks in ((4, (1, 2, 3, 4, 5)), (128, (1, 3, 5)), (256, (1, 2, 4, 6, 7))):
+        for chunk in chunks:
+            say(f"[greedy edge] few steps V+1={V1} {dtype} B={B} chunk={chunk}")
+            got = gpu_greedy(dec, dev.repeat(1, B // 4, 1), np.tile(mids, B // 4), chunk)
+            for i in range(0, B, 4):
+                compare_greedy(got, ref, range(i, i + 4), ATOL, range(4))
+
+
 @pytest.mark.parametrize("V1", [65, 1280, 1281, 2048])
 def test_boundary_fix_up_of_narrow_rows(V1):
     """Calls of several workgroups a stream through the fix-up kernel, on both
@@ -119,7 +143,8 @@ def test_rows_masked_with_a_finite_value(V1, fill, dtype):
 
 
 @pytest.mark.parametrize("V1,dtype,chunk", [(2305, "f32", 14), (2305, "bf16", 1), (8193, "f32", 3),
-                                            (8193, "bf16", 14)])
+                                            (8193, "bf16", 14), (3001, "f32", 4), (6001, "f32", 2),
+                                            (6001, "bf16", 1), (8193, "f32", 1)])
 @pytest.mark.parametrize("seed", [1, 2])
 def test_rows_of_nan_and_of_no_finite_value(V1, dtype, chunk, seed):
     """A nan never wins: tokens and states are the oracle's for the same rows
