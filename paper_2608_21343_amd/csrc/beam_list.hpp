@@ -646,24 +646,26 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
               }
             }
             // the listed moves whose class a child has
-            // and the psi of the deepest such child (the first): the move's
-            // token is a candidate through it
+            uint32_t om = 0u;
 #pragma unroll
             for (int q = 0; q < kList; ++q) {
               const int32_t cq = rl(h.cls, q);
               bool hit = false;
 #pragma unroll
               for (int g = 0; g < NS; ++g) hit = hit || lab[g] == cq;
-              if (__ballot(hit) == 0ull) continue;
-              float pq = 0.f;
+              om |= __ballot(hit) != 0ull ? 1u << q : 0u;
+            }
+            over = ((om >> lane) & 1u) != 0u && lane < kList;
+            // the psi of the deepest such child (the first)
+            for (; om != 0u; om &= om - 1u) {
+              const int32_t q = (int32_t)__builtin_ctz(om), cq = rl(h.cls, q);
 #pragma unroll
               for (int g = NS - 1; g >= 0; --g) {
                 const uint64_t at = __ballot(lab[g] == cq);
-                if (at != 0ull) pq = rlf(h.py[g], (int32_t)__builtin_ctzll(at));
-              }
-              if (lane == q) {
-                over = true;
-                opsi = pq;
+                if (at != 0ull) {
+                  const float pq = rlf(h.py[g], (int32_t)__builtin_ctzll(at));
+                  if (lane == q) opsi = pq;
+                }
               }
             }
             // drop the children that a deeper state's child shadows
@@ -680,12 +682,15 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
         if (h.big) {
           walk_children(h.s, marks_of[i], [](bool, int32_t, int32_t, float) {},
                         [&](bool take, int32_t lab, float py) {
+                          int32_t cls = h.cls;
+                          asm volatile("" : "+v"(cls));  // its lanes are not kept across the walk
                           bool hit = false;
 #pragma unroll
-                          for (int q = 0; q < kList; ++q) hit = hit || lab == rl(h.cls, q);
+                          for (int q = 0; q < kList; ++q) hit = hit || lab == rl(cls, q);
                           if (__ballot(take && hit) == 0ull) return;
+#pragma unroll 1
                           for (int32_t q = 0; q < kList; ++q) {
-                            const uint64_t at = __ballot(take && lab == rl(h.cls, q));
+                            const uint64_t at = __ballot(take && lab == rl(cls, q));
                             if (at == 0ull) continue;
                             const float pq = rlf(py, (int32_t)__builtin_ctzll(at));
                             if (lane == q) opsi = pq;
@@ -1082,7 +1087,7 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
                     (zv - h.lse) + (biased ? px - h.phi : 0.f));
             }
           }
-          constexpr int SC = 8;  // chunks whose loads are in flight together
+          constexpr int SC = NW < 16 ? 4 : 1;  // chunks whose loads are in flight together
           for (int32_t v0 = 0; v0 < V; v0 += 64 * SC) {
             float pc[SC];
             int32_t cc[SC];
