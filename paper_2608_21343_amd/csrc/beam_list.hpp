@@ -246,7 +246,7 @@ struct Slot {
   float lv;     // value of this lane's listed move or blank
 };
 
-// Eight bytes of a logit row, at the alignment of its elements.
+// Sixteen bytes of a logit row, at the alignment of its elements.
 template <class T>
 struct __attribute__((packed, aligned(sizeof(T)))) Quad {
   uint32_t w[4];

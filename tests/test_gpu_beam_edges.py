@@ -24,7 +24,7 @@ EDGES = [2, 3, 256, 257, 512, 513, 768, 769, 1024, 1025, 1280, 1281, 1536, 1537,
 BEAMS = [8, 1, 4, 5, 9, 16, 17, 32, 12, 3]
 
 
-def _run(V1, K, kind, fill, dtype, chunk, T=6):
+def _run(V1, K, kind, fill, dtype, chunk, T=6, atol=ATOL):
     from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
     from workloads.synth import _f32_to_bf16_bits
     K = min(K, V1)
@@ -51,6 +51,8 @@ def _run(V1, K, kind, fill, dtype, chunk, T=6):
         keep[..., V] = rng.random(rows.shape[:-1]) < 0.5
         keep[..., 0] |= ~keep.any(-1)
         rows[~keep] = -np.inf
+    elif fill.startswith("offset"):
+        rows += np.float32(fill[6:])
     elif fill in MASKS:  # 100 tokens kept, all within one wave's share of a row
         keep = np.zeros(V1, bool)
         keep[V1 // 2 - V1 // 2 % 256:][:100] = True
@@ -66,13 +68,13 @@ def _run(V1, K, kind, fill, dtype, chunk, T=6):
     if kind == "plain":
         st0, S0 = oracle.init_carry(mids, K)
         compare_beam(gpu_beam(dec, dev, mids, chunk),
-                     oracle.beam_decode(graphs, mids, rows, st0, S0), range(cfg.B), ATOL)
+                     oracle.beam_decode(graphs, mids, rows, st0, S0), range(cfg.B), atol)
         return
     carry, want = dec.start_beam_stream(mids, K, 24), oracle.init_stream_carry(mids, K)
     for t0 in range(0, T, chunk):
         got = [o.cpu().numpy() for o in dec.beam_stream(dev[t0:t0 + chunk], carry)]
         exp = oracle.beam_decode_stream(graphs, mids, rows[t0:t0 + chunk], want, tree_cap=24)
-        compare_beam(got, exp, range(cfg.B), ATOL)
+        compare_beam(got, exp, range(cfg.B), atol)
 
 
 @pytest.mark.parametrize("i", range(len(EDGES)))
@@ -128,6 +130,17 @@ def test_children_for_most_classes(V1, phrases, members, K):
     got = [o.cpu().numpy() for o in dec.beam_stream(dev, carry)]
     compare_beam(got, oracle.beam_decode_stream(graphs, mids, rows, want, tree_cap=64), range(3),
                  ATOL)
+
+
+@pytest.mark.parametrize("offset", ["+630", "-630", "+650", "-650", "+720", "-720", "+2000", "-2000"])
+@pytest.mark.parametrize("V1", [301, 2305])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_far_from_zero(V1, offset, dtype):
+    """Rows whose sum of exponentials leaves what is summed without a maximum
+    (about e^644 either way), and rows at its edge; accumulated scores bit for
+    bit. Step scores are differences of values up to 2000: 2^-13 each."""
+    for kind in ("plain", "stream"):
+        _run(V1, 4, kind, "offset" + offset, dtype, 3, atol=2.0 ** -12)
 
 
 @pytest.mark.parametrize("fill", MASKS)
