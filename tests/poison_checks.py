@@ -3,10 +3,11 @@ tests/test_gpu_poison.py in a child process).
 
 argv[1] is a directory holding a copy of the package whose library is the
 poison build; it goes first on sys.path. Every kernel family runs once on a
-small case: greedy short-call, segmented with fix-up, wide-row and reference
-kernels; beam one-wave-per-hypothesis (with its row preparation), helper-wave,
-wide-row and reference kernels; the streaming beam on the fast and the
-reference kernel; a variative graph."""
+small case: the greedy short-call, segmented and fix-up kernels, wide rows in
+calls of few steps and through row summaries and walk, and the reference
+kernel; the beam's row summaries (one and four waves a row) and its step kernel
+in every layout of waves (4, 8, 16, and two slots a wave; rows in LDS and in
+memory), plain and streaming, and its reference kernel; a variative graph."""
 
 import os
 import sys
@@ -87,14 +88,16 @@ def variative():
 
 greedy(300, 48, 16)                                   # short-call kernel
 greedy(300, 200, 200)                                 # segmented kernel + fix-up
-greedy(3000, 96, 96, "bf16")                          # wide-row kernel
+greedy(3000, 6, 2)                                    # wide rows, few steps
+greedy(3000, 96, 96, "bf16")                          # row summaries and walk
+greedy(3000, 40, 40)
 greedy(300, 48, 16, kernel=capi.GREEDY_REF)           # reference kernel
-beam(300, 8, 40)                                      # row preparation + one wave per hypothesis
-beam(3000, 4, 24, "bf16")                             # helper waves
-beam(3000, 8, 24, kernel=capi.BEAM_NO_PIPE)           # wide-row kernel
+for V, dtype in ((300, "f32"), (3000, "bf16")):
+    for K in (3, 8, 12, 32):                          # 4, 8 and 16 waves, two slots a wave
+        beam(V, K, 24, dtype)
+        stream_beam(V, K, 24)
 beam(300, 5, 24, kernel=capi.BEAM_REF)                # reference kernel
-stream_beam(300, 8, 32)                               # streaming stage, fast kernel
-stream_beam(300, 4, 32, kernel=capi.BEAM_REF)         # streaming stage, reference kernel
+stream_beam(300, 4, 32, kernel=capi.BEAM_REF)
 capi.tb_debug_select_kernels(capi.GREEDY_AUTO, capi.BEAM_AUTO)
 variative()
 print("poison checks: ok", flush=True)

@@ -1,7 +1,9 @@
 """Vocabularies at both ends of what the boundary accepts, one token plus the
 blank (V+1 = 2) and V+1 = 32768, through the greedy and beam step calls,
 against the oracle. The dispatch picks the kernels; at V+1 = 32768 these are
-the reference kernels, whose per-class override table must fit the LDS.
+the last instances of the row summaries, with the longest class bitmaps of the
+walk and of the beam step in LDS, and the largest vocabulary is also run through
+the reference kernels, whose per-class override table must fit there.
 
 Phrases are planted in the logits, so the biased moves are taken; a stream
 on model -1 and one on an empty list ride along."""
@@ -90,11 +92,15 @@ def _largest():
 
 
 @pytest.mark.parametrize("K,dtype,chunk", [(1, "f32", 24), (1, "bf16", 7), (2, "f32", 24),
-                                           (3, "bf16", 10)])
+                                           (3, "bf16", 10), (32, "bf16", 24)])
 def test_largest_vocabulary(K, dtype, chunk):
     V, cm, lists = _largest()
-    say(f"[extremes] V+1 = {V + 1} K={K} {dtype} chunk={chunk}")
-    _run(V, cm, lists, [0, 1, 2, 3, -1], T=24, K=K, seed=3, plant=5.0, dtype=dtype, chunk=chunk)
+    for ref in (False, True):
+        say(f"[extremes] V+1 = {V + 1} K={K} {dtype} chunk={chunk} reference={ref}")
+        with capi.kernels(greedy=capi.GREEDY_REF if ref else capi.GREEDY_AUTO,
+                          beam=capi.BEAM_REF if ref else capi.BEAM_AUTO):
+            _run(V, cm, lists, [0, 1, 2, 3, -1], T=24, K=K, seed=3, plant=5.0, dtype=dtype,
+                 chunk=chunk)
 
 
 def test_largest_vocabulary_is_the_limit():
@@ -106,8 +112,8 @@ def test_largest_vocabulary_is_the_limit():
 
 
 def test_largest_vocabulary_streaming_beam():
-    """The streaming beam (recombination and tree) at V+1 = 32768: the
-    reference kernel's stage, chunk by chunk against the oracle's."""
+    """The streaming beam (recombination and tree) at V+1 = 32768, chunk by
+    chunk against the oracle's."""
     from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
     V, cm, lists = _largest()
     mids = np.asarray([0, 1, 2, 3, -1], np.int32)

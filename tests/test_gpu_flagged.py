@@ -89,7 +89,7 @@ def test_records_are_flagged_where_expected():
 
 
 GREEDY_KERNEL = {"default": capi.GREEDY_AUTO, "ref": capi.GREEDY_REF}
-BEAM_KERNEL = {"default": capi.BEAM_AUTO, "wide": capi.BEAM_NO_PIPE, "ref": capi.BEAM_REF}
+BEAM_KERNEL = {"default": capi.BEAM_AUTO, "ref": capi.BEAM_REF}
 T_STEPS = 320
 
 
@@ -112,7 +112,7 @@ def test_greedy_through_flagged_records(kernel, V, chunk, fan, restore_kernels):
 
 @pytest.mark.parametrize("kernel,V,K,fan", [("default", 1024, 4, 300), ("default", 1024, 8, 300),
                                             ("ref", 1024, 4, 300), ("default", 2600, 4, 300),
-                                            ("wide", 2600, 4, 300), ("default", 1024, 4, 30),
+                                            ("default", 2600, 12, 300), ("default", 1024, 4, 30),
                                             ("default", 1024, 8, 30), ("default", 2600, 4, 30),
                                             ("default", 1024, 4, 250), ("default", 1024, 8, 250)])
 def test_beam_through_flagged_records(kernel, V, K, fan, restore_kernels):

@@ -387,7 +387,7 @@ def test_chunk_loop_graph_replay_matches_eager():
             assert torch.equal(a, b), f"replay {rep} differs from the eager run"
 
 
-BEAM_KERNEL = {"default": capi.BEAM_AUTO, "wide": capi.BEAM_NO_PIPE, "ref": capi.BEAM_REF}
+BEAM_KERNEL = {"default": capi.BEAM_AUTO, "ref": capi.BEAM_REF}
 
 
 @pytest.mark.parametrize("kernel", ["default", "ref"])
@@ -418,7 +418,7 @@ def test_beam_kernels_match_oracle_on_mixed_streams(kernel, K, dtype, restore_ke
 
 
 @pytest.mark.parametrize("kernel,V,K", [("default", 300, 3), ("default", 300, 8), ("ref", 300, 3),
-                                        ("default", 2600, 4), ("wide", 2600, 4)])
+                                        ("default", 2600, 4), ("default", 2600, 12)])
 def test_beam_bad_carried_states_decode_unbiased(kernel, V, K, restore_kernels):
     """A valid model id with a carried state out of range, TB_STATE_INVALID or
     TB_STATE_TIMEOUT in one of its slots: the stream is decoded without
@@ -519,7 +519,8 @@ def test_greedy_bad_carried_states_decode_unbiased(kernel, V, chunk, restore_ker
     ("default", 300, 1, 16), ("default", 300, 1, 96), ("ref", 300, 1, 16),
     ("default", 2600, 1, 16), ("default", 2600, 1, 96),
     ("default", 300, 3, 96), ("default", 300, 8, 40), ("ref", 300, 3, 96),
-    ("default", 2600, 4, 96), ("wide", 2600, 4, 96), ("stream", 300, 3, 32)])
+    ("default", 2600, 4, 96), ("default", 2600, 12, 96), ("stream", 300, 3, 32),
+    ("default", 2600, 1, 2)])
 def test_padded_row_stride_every_kernel(kernel, V, K, chunk, restore_kernels):
     """Rows farther apart than V+1 (seven values of 1e30 after each row, which
     any read of them would make win) through every greedy and beam kernel and
@@ -560,9 +561,9 @@ def test_padded_row_stride_every_kernel(kernel, V, K, chunk, restore_kernels):
 @pytest.mark.parametrize("V", [2046, 2047, 2048])
 @pytest.mark.parametrize("K,chunk", [(1, 16), (1, 100), (4, 100), (8, 50)])
 def test_rows_at_the_wide_kernel_boundary(V, K, chunk):
-    """V+1 = 2047, 2048 (the widest rows of the one-wave-per-row kernels) and
-    2049 (the narrowest of the wide-row kernels), greedy in short and long
-    calls and beam, against the oracle."""
+    """V+1 = 2047, 2048 (the widest rows of the narrow greedy kernels and of one
+    wave per row in the beam summaries) and 2049 (the narrowest of the wide
+    ones), greedy in short and long calls and beam, against the oracle."""
     from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
     cfg, lists, rows = _small_case(12, B=4, V=V, n_case=V // 9, K=K, T=100, dtype="bf16")
     dec = BoostDecoder(lists, W.class_map(cfg), token_w=cfg.token_w, end_bonus=cfg.end_bonus)
@@ -625,10 +626,9 @@ def test_beam_inside_long_phrases(kernel, restore_kernels):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_wide_vocabulary_mixed_streams_and_chunks(dtype, restore_kernels):
-    """Wide rows (V+1 = 3001, not a multiple of 256): the workgroup-segmented
-    kernel against the oracle with model -1, an empty list and an
-    out-of-range id, for whole calls (several segments per stream and the
-    boundary fix-up) and chunked calls; tokens, states and carries equal the
+    """Wide rows (V+1 = 3001, not a multiple of 256): row summaries and walk
+    against the oracle with model -1, an empty list and an out-of-range id,
+    for whole calls (several segments per stream) and chunked calls; tokens, states and carries equal the
     reference kernel's."""
     from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
     cfg = W.Config(107, "small", B=7, K=1, V=3000, T=96, chunk=96, dtype=dtype, n_phrases=200,
@@ -682,10 +682,10 @@ def test_wide_vocabulary_segments_inside_long_phrases():
     assert np.max(ref[1][:, 0]) >= 30
 
 
-@pytest.mark.parametrize("kernel", ["default", "wide"])
-@pytest.mark.parametrize("K,dtype", [(3, "f32"), (4, "bf16"), (8, "bf16")])
+@pytest.mark.parametrize("kernel", ["default"])
+@pytest.mark.parametrize("K,dtype", [(3, "f32"), (4, "bf16"), (8, "bf16"), (20, "f32")])
 def test_wide_vocabulary_beam_mixed_streams(kernel, K, dtype, restore_kernels):
-    """Beam kernels on wide rows (V+1 = 3001) against the oracle: model -1, an
+    """The beam kernel on wide rows (V+1 = 3001) against the oracle: model -1, an
     empty list and an out-of-range id (decoded unbiased, states -2), chunked
     calls equal one call, and the reference kernel agrees."""
     from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
@@ -743,12 +743,12 @@ def test_beam_tiny_vocabulary(kernel, K, restore_kernels):
     compare_beam(gpu, ref, range(B), ATOL)
 
 
-@pytest.mark.parametrize("kernel", ["default", "wide"])
-@pytest.mark.parametrize("K,dtype", [(4, "bf16"), (2, "f32")])
+@pytest.mark.parametrize("kernel", ["default"])
+@pytest.mark.parametrize("K,dtype", [(4, "bf16"), (2, "f32"), (12, "f32")])
 def test_wide_vocabulary_beam_inside_long_phrases(kernel, K, dtype, restore_kernels):
     """Wide rows (V+1 = 2601) with hypotheses deep inside 40-token phrases
     whose tokens have the largest logits: most of a row's listed root moves
-    are overridden, so the helper-wave kernel rescans rows too."""
+    are overridden, so rows are scanned past their lists too."""
     from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
     capi.tb_debug_select_kernels(beam=BEAM_KERNEL[kernel])
     V, B, T = 2600, 4, 120

@@ -115,19 +115,22 @@ def test_stream_beam_matches_the_oracle(K, V, dtype):
 
 @pytest.mark.parametrize("K,V,dtype", [(4, 3000, "f32"), (12, 500, "f32"), (3, 5000, "bf16"),
                                        (32, 300, "f32")])
-def test_stream_beam_on_the_reference_kernel(K, V, dtype):
-    """Rows wider than 2048 and beams wider than 8: the reference kernel's
-    streaming stage."""
+def test_stream_beam_on_the_reference_kernel(K, V, dtype, restore_kernels):
+    """Rows wider than 2048 and beams wider than 8, through the step kernel and
+    through the reference kernel's streaming stage."""
+    from paper_2608_21343_amd import capi
     cfg = _cfg(K * 7 + V, B=6, K=K, V=V, T=32, dtype=dtype)
     mids = np.arange(cfg.B, dtype=np.int32)
     mids[2] = -1
     say(f"[stream-beam-ref] K={K} V={V} {dtype}: merges on {_merges(cfg, mids)} stream-steps")
     _run(cfg, mids, chunk=16)
+    capi.tb_debug_select_kernels(beam=capi.BEAM_REF)
+    _run(cfg, mids, chunk=16)
 
 
 def test_stream_beam_reference_kernel_forced(restore_kernels):
-    """The reference kernel's streaming stage on a row the fast kernel would
-    take, forced through the test hook."""
+    """The reference kernel's streaming stage on a narrow row, forced through
+    the test hook."""
     from paper_2608_21343_amd import capi
     capi.tb_debug_select_kernels(beam=capi.BEAM_REF)
     cfg = _cfg(77, B=8, K=8, V=700, T=32)
