@@ -376,10 +376,20 @@ RowsLaunch rows_launcher_t(int32_t V1) {
 // LDS of the step kernel: the rows (ROWS), the class bitmaps, and with what
 // is left records of the model's first states. Records are filled once a
 // call (20 bytes read per state) and save a trip to the cache per step, so a
-// call of fewer than kHotSteps steps does without.
-constexpr int kHotSteps = 4;
+// call of fewer than kHotSteps steps does without: with / without them, 64
+// streams, 4 hypotheses of 1024 float32, calls of 4, 12, 16, 32 and 64 steps take
+// 33 / 30, 64 / 62, 81 / 78, 149 / 149 and 269 / 272 us, 8 hypotheses 38 / 37, 77 / 76,
+// 98 / 99, 182 / 185 and 329 / 334, 4 of 8192 bfloat16 48 / 44, 100 / 98, 124 / 123,
+// 226 / 229 and 431 / 439. (A model with a record that does not fit, such as a state
+// of 255 children, runs without them: these figures are what that costs.)
+constexpr int kHotSteps = 16;
 constexpr int kLdsBytes = 160 * 1024;
-constexpr int kMostRows = 72 * 1024;  // LDS given to rows; the records need the rest
+// LDS given to rows; the records need the rest. Rows in LDS against rows gathered
+// from memory, calls of 32 steps: 177 / 196 us (8 hypotheses of 1024 float32, 33 KB),
+// 147 / 168 (4 of 500 bfloat16), 205 / 208 (8 of 2000 float32, 64 KB); 16 of 1000
+// float32 (64 KB) 334 / 333, and above the line 379 / 358 (12 of 2000 float32, 96 KB)
+// and 512 / 490 (16 of them, 128 KB).
+constexpr int kMostRows = 72 * 1024;
 
 inline int32_t row_bytes(int32_t V1, size_t item) {
   return (int32_t)(((size_t)V1 * item + 15) / 16 * 16);

@@ -51,8 +51,15 @@ using blist::rl;
 using blist::rlf;
 using blist::sload;
 
-constexpr int kBest = 4;  // root moves listed per row
-constexpr int kWarm = 4;  // warm-up rows of a guessed segment start
+// Root moves listed per row: two words of a row's outputs hold four. With two the
+// row is scanned more often: 32 streams of 64 rows of 4097 float32 61 us against 52,
+// 256 streams of 64 rows of 8193 bfloat16 169 against 154.
+constexpr int kBest = 4;
+// Warm-up rows of a guessed segment start. Two, four and seven measure within the
+// spread of one another over lists of 1000 and 5000 phrases (128 streams of 64 rows
+// of 4097 float32: 83, 81, 81 and 140, 125, 137 us; 256 rows: 195, 197, 204 and 257,
+// 260, 263).
+constexpr int kWarm = 4;
 constexpr int kRowThreads = 256;
 constexpr int kWalkThreads = 1024;
 constexpr int kLevels = 4;  // chain states whose children are taken one per lane
@@ -803,7 +810,11 @@ Launch launcher_f32(int32_t V1);
 Launch launcher_bf16(int32_t V1);
 
 constexpr int kLdsBytes = 152 * 1024;
-constexpr int kHotRows = 4;  // rows a wave must have for the records to be worth their filling
+// Steps of a call from which the records are worth their filling: with / without
+// them calls of 6, 8, 12 and 16 steps take 32 / 30, 34 / 34, 45 / 46 and 51 / 53 us (128
+// streams, 4097 float32), 45 / 41, 48 / 47, 61 / 61 and 70 / 72 (256 streams, 8193
+// bfloat16); 64 steps 81 / 84 and 154 / 156.
+constexpr int kHotSteps = 12;
 
 template <class Ld, int NWR, int NP, int NC>
 hipError_t launch_t(const ArenaView& A, const void* logits, int32_t T, int32_t B, int64_t stride,
@@ -833,7 +844,7 @@ hipError_t launch_t(const ArenaView& A, const void* logits, int32_t T, int32_t B
     const int32_t n = T - t < most ? T - t : most;
     const int32_t L = (n + kWaves - 1) / kWaves, waves = (n + L - 1) / L;
     const int32_t room = kLdsBytes - n * (int32_t)sizeof(RowRec) - 4 * waves * words;
-    int32_t hot = L >= kHotRows ? (room / 16 < 8192 ? room / 16 : 8192) : 0;
+    int32_t hot = n >= kHotSteps ? (room / 16 < 8192 ? room / 16 : 8192) : 0;
     if (hot > A.n_states) hot = (int32_t)A.n_states;
     const int32_t lds = kLdsBytes - room + 16 * hot;
     // streams [b0, B) in launches of as many workgroups as one may have

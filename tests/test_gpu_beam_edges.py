@@ -80,14 +80,16 @@ def _run(V1, K, kind, fill, dtype, chunk, T=6, atol=ATOL):
 @pytest.mark.parametrize("i", range(len(EDGES)))
 def test_row_instance_edges(i):
     _run(EDGES[i], BEAMS[i % len(BEAMS)], ("plain", "stream")[i % 2], "normal",
-         ("f32", "bf16")[i // 2 % 2], (6, 2)[i // 3 % 2])
+         ("f32", "bf16")[i // 2 % 2], (17, 3)[i // 3 % 2], T=17)
 
 
 @pytest.mark.parametrize("K", [1, 4, 5, 8, 9, 16, 17, 32])
 @pytest.mark.parametrize("kind", ["plain", "stream"])
 def test_wave_layouts(K, kind):
     _run(601, K, kind, "normal", "f32", 6, T=10)
+    _run(601, K, kind, "normal", "bf16", 20, T=20)
     _run(2600, K, kind, "normal", "bf16", 10, T=10)
+    _run(2600, K, kind, "normal", "f32", 20, T=20)
 
 
 @pytest.mark.parametrize("K", [3, 8, 16, 32])
@@ -106,7 +108,7 @@ def test_children_for_most_classes(V1, phrases, members, K):
     overridden, by children held one per lane and by larger sets."""
     from paper_2608_21343_amd.decoder import BoostDecoder, to_device_logits
     say(f"[beam edge] dense lists V+1={V1} phrases={phrases} members={members} K={K}")
-    V, T = V1 - 1, 10
+    V, T = V1 - 1, 18
     cfg = W.Config(8400 + V1 + K, "dense", B=3, K=K, V=V, T=T, chunk=T, dtype="f32",
                    n_phrases=phrases, len_lo=1, len_hi=6, token_dist="zipf", zipf_s=1.1,
                    logit_std=1.5, blank_offset=0.5, n_case=V // 9)
@@ -124,7 +126,7 @@ def test_children_for_most_classes(V1, phrases, members, K):
               for m in (0, 1)}
     dev = to_device_logits(rows)
     st0, S0 = oracle.init_carry(mids, K)
-    compare_beam(gpu_beam(dec, dev, mids, 5), oracle.beam_decode(graphs, mids, rows, st0, S0),
+    compare_beam(gpu_beam(dec, dev, mids, 9), oracle.beam_decode(graphs, mids, rows, st0, S0),
                  range(3), ATOL)
     carry, want = dec.start_beam_stream(mids, K, 64), oracle.init_stream_carry(mids, K)
     got = [o.cpu().numpy() for o in dec.beam_stream(dev, carry)]
