@@ -19,7 +19,7 @@
 // instead of scoring K*(V+1) candidates: a step is some 10 thousand cycles
 // (8 hypotheses, 1024 tokens: 4.1 us against 7.0 us when every wave scored its
 // whole row; 32 hypotheses: 11 us against 920 us for the reference kernel, which
-// took beams above 8 before; 4 hypotheses of 8192 tokens: 11 us against 26 us
+// took beams above 8 before; 4 hypotheses of 8192 tokens: 8 us against 26 us
 // with the rows summarised inside the step). Per step, wave w (slots w and, for
 // more than 16 hypotheses, w + 16):
 //
@@ -153,6 +153,7 @@ struct alignas(16) Shared {
   int32_t first_bound;
   int32_t count[2];
   int32_t rank[2][64];
+  float opsi[NW][kList];  // psi of the children that override listed moves (large sets)
   float vpsi[256], vphi[256];
 };
 
@@ -680,23 +681,39 @@ __global__ __launch_bounds__(64 * NW) void beam_list_kernel(
           }
         }
         if (h.big) {
+          // The psi of the children that have a listed move's class. Narrow rows of
+          // few waves look the moves up one by one (stream of 5 hypotheses of 1000
+          // tokens 536 us a pass against 547 through LDS); else the child leaves
+          // its psi in LDS, at the last such move (32 hypotheses: 395 against 406).
+          constexpr bool kThroughLds = NW == 16 || !ROWS;
+          float* ob = S.opsi[w];
           walk_children(h.s, marks_of[i], [](bool, int32_t, int32_t, float) {},
                         [&](bool take, int32_t lab, float py) {
                           int32_t cls = h.cls;
                           asm volatile("" : "+v"(cls));  // its lanes are not kept across the walk
-                          bool hit = false;
+                          int32_t at = -1;
 #pragma unroll
-                          for (int q = 0; q < kList; ++q) hit = hit || lab == rl(cls, q);
-                          if (__ballot(take && hit) == 0ull) return;
+                          for (int q = 0; q < kList; ++q) at = lab == rl(cls, q) ? q : at;
+                          if constexpr (kThroughLds) {
+                            if (take && at >= 0) ob[at] = py;
+                          } else {
+                            if (__ballot(take && at >= 0) == 0ull) return;
 #pragma unroll 1
-                          for (int32_t q = 0; q < kList; ++q) {
-                            const uint64_t at = __ballot(take && lab == rl(cls, q));
-                            if (at == 0ull) continue;
-                            const float pq = rlf(py, (int32_t)__builtin_ctzll(at));
-                            if (lane == q) opsi = pq;
+                            for (int32_t q = 0; q < kList; ++q) {
+                              const uint64_t who = __ballot(take && lab == rl(cls, q));
+                              if (who == 0ull) continue;
+                              const float pq = rlf(py, (int32_t)__builtin_ctzll(who));
+                              if (lane == q) opsi = pq;
+                            }
                           }
                         });
           over = h.cls >= 0 && lane < kList && marked(marks_of[i], h.cls);
+          if constexpr (kThroughLds) {
+            int32_t at = 0;
+#pragma unroll
+            for (int q = 0; q < kList; ++q) at = h.cls == rl(h.cls, q) ? q : at;
+            if (over) opsi = ob[at];
+          }
         }
       }
       h.c = (Sk - h.lse) - h.phi;

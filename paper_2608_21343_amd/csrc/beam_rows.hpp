@@ -14,13 +14,12 @@
 //
 // One wave per row up to 2048 values, four waves above. The kernel is bound
 // by vector instructions, most of them the exponentials (21 a value, 13 in
-// float64; 131,072 rows of 1025 float32 took 192 us, 65,536 of 8193 bfloat16
-// 650 us, where reading them takes 104 and 207 us at a copy's rate; with one
-// test for the unused chunks and one for eight values without a best move, the
-// calls of these rows take 0 and 4 to 8 % less). So the sum is taken of e^z itself, not of e^(z - max), so that
-// the row is passed once and no value waits for a maximum; float64 holds
-// e^z for |z| <= 700, and a row whose sum leaves [1e-280, 1e280] (or holds a
-// nan) is summed again relative to its maximum.
+// float64): 131,072 rows of 1025 float32 take 197 us, 65,536 of 8193 bfloat16
+// 569 us, where reading them takes 104 and 207 us at a copy's rate. The sum is
+// taken of e^z itself, not of e^(z - max), so that the row is passed once and no
+// value waits for a maximum; float64 holds e^z for |z| <= 700, and a row whose
+// sum leaves [1e-280, 1e280] (or holds a nan) is summed again relative to its
+// maximum.
 #pragma once
 
 #include <climits>
@@ -380,7 +379,8 @@ RowsLaunch rows_launcher_t(int32_t V1) {
 // streams, 4 hypotheses of 1024 float32, calls of 4, 12, 16, 32 and 64 steps take
 // 33 / 30, 64 / 62, 81 / 78, 149 / 149 and 269 / 272 us, 8 hypotheses 38 / 37, 77 / 76,
 // 98 / 99, 182 / 185 and 329 / 334, 4 of 8192 bfloat16 48 / 44, 100 / 98, 124 / 123,
-// 226 / 229 and 431 / 439. (A model with a record that does not fit, such as a state
+// 226 / 229 and 431 / 439; 32 hypotheses of 1000 float32, calls of 4 and 8 steps 93 / 94
+// and 264 / 267, so above 16 hypotheses four steps are enough. (A model with a record that does not fit, such as a state
 // of 255 children, runs without them: these figures are what that costs.)
 constexpr int kHotSteps = 16;
 constexpr int kLdsBytes = 160 * 1024;
@@ -407,7 +407,7 @@ inline Layout make_layout(const ArenaView& A, int32_t T, int32_t K, size_t item,
   l.mark_words = (A.V1 + 31) / 32;
   l.hot = (l.marks + 4 * K * l.mark_words + 15) / 16 * 16;
   const int64_t room = (kLdsBytes - 1024 - (int64_t)fixed - l.hot) / 16;
-  l.nhot = (T >= kHotSteps && room > 0) ? (int32_t)(room < 8192 ? room : 8192) : 0;
+  l.nhot = (T >= (K > 16 ? 4 : kHotSteps) && room > 0) ? (int32_t)(room < 8192 ? room : 8192) : 0;
   if (l.nhot > A.n_states) l.nhot = (int32_t)A.n_states;
   l.total = l.hot + 16 * l.nhot;
   return l;

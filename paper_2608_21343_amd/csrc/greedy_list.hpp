@@ -5,8 +5,9 @@
 // A call over wide rows should cost one read of the logits. What kept it
 // from that was the scoring of every token from the current state, row after
 // row (12 thousand cycles a row of 8192 tokens; 256 streams of 256 bfloat16
-// rows took 2.40 ms, now 0.39 ms for the summaries and 0.23 ms for the walk,
-// where reading the rows takes 0.21 ms). Only the children along the
+// rows took 2.40 ms, now 0.37 ms for the summaries and 0.18 ms for the walk,
+// where reading the rows takes 0.21 ms). Calls of very few steps are the
+// exception (greedy_wide.hip). Only the children along the
 // state's suffix chain depend on the state; the normaliser and the best root
 // moves do not, and are taken for all rows at once:
 //
