@@ -1488,8 +1488,8 @@ __global__ __launch_bounds__(Shape<PER>::NT) void greedy_seg_kernel(
 // until the stored trajectory is met. All waves fill the tables, wave 0
 // repairs. Writes the carry.
 // The fill bounds the kernel, and it is bound by the loads a CU has in flight:
-// a launch over rows of 1025 float32 takes 12.0 us with sixteen waves and took
-// 18.4 us with four (mean of 32 streams of 500 rows and 128 of 1024). The
+// a launch over rows of 1025 float32 takes 16 us with sixteen waves and 19 with
+// four for 32 streams of 500 rows, 22 and 29 for 128 streams of 1024. The
 // repairing wave's three row buffers need more than the 128 registers that
 // sixteen waves leave it above 20 chunks: eight there.
 template <int PER>
