@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kRowThreads) void greedy_rows_kernel(
   constexpr int kWaves = kRowThreads / 64, kRows = kWaves / NWR;
   constexpr int PV = 16 / sizeof(LT), NF = NP * PV, NZ = NF + NC;
   __shared__ uint64_t g_key[kRows][64];  // moves in (value, token) order: order_key, ~token
-  __shared__ float g_sum[kWaves], g_max[kWaves], g_top[kWaves][64];
+  __shared__ float g_sum[kWaves], g_max[kWaves], g_shift[kWaves], g_top[kWaves][64];
   __shared__ int32_t g_count[kRows];
   lds_poison(g_key, sizeof(g_key));
   lds_poison(g_top, sizeof(g_top));
@@ -168,16 +168,18 @@ __global__ __launch_bounds__(kRowThreads) void greedy_rows_kernel(
 #pragma unroll
   for (int g = 0; g < NG; ++g) top = __builtin_fmaxf(top, group[g]);
   // The wave's sum relative to its own maximum. The exponent z log2(e) - mL is
-  // one instruction and off by the rounding of mL alone, so the sum is rescaled
-  // by it. Where that rounding is not small (a wave of nothing but mask values
-  // such as -1e30, where it exceeds every exponent) the maximum is subtracted
-  // first. Largest error of the step scores against float64, 4096 rows of 8193
-  // float32 of deviation 1.5 around 0, 20, 100, 1000: 1.0e-6, 1.5e-6, 4.3e-6,
-  // 3.1e-5 (without the rescaling 1.1e-6, 2.5e-6, 8.5e-6, 6.3e-5).
+  // one instruction and off by the rounding of mL alone, which is taken out
+  // where the waves' sums are added up. Where that rounding is not small (a wave
+  // of nothing but mask values such as -1e30, where it exceeds every exponent)
+  // the maximum is subtracted first. Largest error of the step scores against
+  // float64, 4096 rows of 8193 float32 of deviation 1.5 around 0, 20, 100, 1000:
+  // 1.1e-6, 1.5e-6, 4.3e-6, 3.1e-5 (with that rounding left in 1.1e-6, 2.5e-6,
+  // 8.5e-6, 6.3e-5).
+  static_assert(NWR > 1, "the factors of the waves' sums take the shift out");
   zm = wave_max_dpp(zm);
   const float ref = zm == kNegInf ? 0.f : zm;  // no finite value: the terms are 0 (or nan)
   auto exp_of = [](float x) { return __builtin_amdgcn_exp2f(x * kLog2e); };
-  float se = 0.f;
+  float se = 0.f, shift = 0.f;  // the sum is 2^shift times too large
   auto sum = [&](auto term) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {  // a piece at a time: less rounding than one chain
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(kRowThreads) void greedy_rows_kernel(
   if (__builtin_fabsf(ref) < 8192.f) {  // uniform
     const float mL = ref * kLog2e;
     sum([&](float x) { return __builtin_amdgcn_exp2f(__builtin_fmaf(x, kLog2e, -mL)); });
-    se *= __builtin_amdgcn_exp2f(-__builtin_fmaf(ref, kLog2e, -mL));
+    shift = __builtin_fmaf(ref, kLog2e, -mL);
   } else {
     sum([&](float x) { return exp_of(x - ref); });
   }
@@ -202,6 +204,7 @@ __global__ __launch_bounds__(kRowThreads) void greedy_rows_kernel(
     if (lane == 0) {
       g_sum[wv] = se;
       g_max[wv] = zm;
+      g_shift[wv] = shift;
     }
     if (threadIdx.x == 0) g_count[0] = 0;
     __syncthreads();
@@ -215,7 +218,8 @@ __global__ __launch_bounds__(kRowThreads) void greedy_rows_kernel(
 #pragma unroll
     for (int i = 0; i < NWR; ++i) {
       const float mi = g_max[i];  // -inf: the wave's sum is 0 (or nan, which stays)
-      se += g_sum[i] * (mi == kNegInf ? 0.f : exp_of(mi - zm));
+      se += g_sum[i] *
+            (mi == kNegInf ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(mi - zm, kLog2e, -g_shift[i])));
     }
   }
   const float lse = zm + __logf(se);
